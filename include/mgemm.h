@@ -84,12 +84,12 @@ enum {
  *   elems_per_thread  contiguous elements one thread copies per global->LDS
  *                     load (the paper's element layer).
  *   double_buffer     1: two LDS stages, the next k-step's tiles are loaded while
- *                     the current one is multiplied; 0: one stage; 2: three
- *                     stages filled by direct global->LDS loads two k-steps
- *                     ahead (needs n, lda and ldb multiples of the 16-byte load,
- *                     2 FP64 or 4 FP32 elements, and 16-byte aligned A and B,
- *                     else the two-stage kernel of the same tile runs, with the
- *                     same results).
+ *                     the current one is multiplied; 0: one stage; 2: two
+ *                     stages filled by direct global->LDS loads, two k-steps
+ *                     ahead of the products (needs n of at least one 16-byte
+ *                     load, 2 FP64 or 4 FP32 elements, and A and B on 4-byte
+ *                     boundaries, else the register-staged kernel of the same tile
+ *                     runs, with the same results).
  *   occupancy         wavefronts per SIMD the kernel is compiled to allow (0: the
  *                     compiler's choice, else 1 or 2) -- the GPU counterpart of
  *                     the paper's hardware threads per core (Sec. 3, Tab. 4).
@@ -112,25 +112,30 @@ MGEMM_API int32_t gemm(int64_t m, int64_t n, int64_t k, double alpha,
  * still gives enough work-groups for the m x n output; split-k below where k >=
  * 2048 or m, n or k lies outside [64, 16384]; otherwise, with a cost model loaded
  * (mgemm_model_load) and m, n, k in [64, 16384], its prediction; else, for rows
- * the three-stage kernels can load (n, lda, ldb multiples of 16 bytes, A and B
- * 16-byte aligned), the three-stage tile (256 x 128, 128 x 128 or 64 x 64) whose
+ * of whole 16-byte loads (n, lda, ldb multiples of 16 bytes, A and B
+ * 16-byte aligned), the direct-load tile (256 x 128, 128 x 128 or 64 x 64) whose
  * sustained rate times the fill of its rounds of one work-group per compute unit
  * is highest, if that fill is at least 80 % -- or, where 128 x 128 tiles leave a
  * last round of few tiles, the tile rows that fill whole rounds whole and the
  * remaining rows with k cut (a split tail), where that is estimated 5 % faster
  * than the best single tile (2 % where that tile is 128 x 128 or 256 x 128);
  * else (m, n, k in [64, 16384]), for
- * rows the three-stage kernels cannot load or where the preferred tile is a
+ * other rows or where the preferred tile is a
  * two-stage one, the configuration measured fastest on the tuner's shapes of the
  * same row class in and around the (floor(log2 m), floor(log2 n), floor(log2 k))
  * cell.
+ * Every configuration sums k in the same order, so what a choice fixes is the split
+ * of k: the whole products and k ranges of the built-in choice (no cfg, no model)
+ * are executed by the direct-load tile estimated fastest for their shape, rows of
+ * any alignment, with the bits of the configuration chosen; the chosen one itself
+ * runs where the direct loads cannot (see double_buffer).
  *
  * Split-k (MGEMM_F64 and MGEMM_F32, cfg == NULL only, k >= 2048 or outside the
  * measured range): when the preferred tile leaves fewer than about four
  * work-groups per compute unit and k >= 512, k is
- * cut into S <= 16 ranges (multiples of 256; computed with the three-stage
- * 128 x 128 tile where its requirements hold and it fills the GPU, else, for
- * MGEMM_F64 only, with the chosen tile); their partial products go to the library-owned
+ * cut into S <= 16 ranges (multiples of 256; counted for the
+ * 128 x 128 tile where rows are whole 16-byte loads and it fills the GPU, else, for
+ * MGEMM_F64 only, for the chosen tile); their partial products go to the library-owned
  * device workspace (S*m*n*8 bytes, S*m*n*4 for FP32, grown on demand, MGEMM_ERR_NOMEM if it
  * cannot be, kept until mgemm_release_workspace(); calls on one device that use
  * it are ordered through it) and one kernel adds them in range order and applies
@@ -347,8 +352,9 @@ MGEMM_API int32_t mgemm_config_get(int32_t dtype, int32_t i, mgemm_cfg *out);
 #define MGEMM_CFG_SPLITK 4
 MGEMM_API int32_t mgemm_config_flags(int32_t dtype, int32_t i);
 
-/* The tile configuration gemm_ex with cfg == NULL runs for an m x n x k product
- * of dtype (MGEMM_F64 or MGEMM_F32) whose A and B are 16-byte aligned with leading
+/* The tile configuration gemm_ex with cfg == NULL chooses for an m x n x k product
+ * of dtype (MGEMM_F64 or MGEMM_F32; its results are that configuration's bit for
+ * bit, see gemm_ex) whose A and B are 16-byte aligned with leading
  * dimensions lda and ldb, on the current device (its compute units enter the
  * choice); a loaded model enters only through the choices it has cached.  *splits
  * receives the number of k ranges (1: k is not cut; above 1 the ranges run the

@@ -194,7 +194,7 @@ static const KernelEntry *measured_entry(int32_t dtype, bool rows16, int64_t m, 
     return find_entry(reg, cnt, cfg);
 }
 
-// Whether the three-stage kernels can load these rows (16-byte rows and bases).
+// Whether the rows of A and B are whole 16-byte loads (16-byte rows and bases).
 static bool rows_whole_loads(const GemmArgs &a, int32_t dtype) {
     const int64_t epu = dtype == MGEMM_F32 ? 4 : 2;
     return a.n % epu == 0 && a.lda % epu == 0 && a.ldb % epu == 0 &&
@@ -263,10 +263,10 @@ static bool capturing(hipStream_t s) {
 // cut into S ranges of kc values (a multiple of SPLITK_MIN_K, itself a multiple of
 // every tile's BK; the last range is the short one); the S partial products go to
 // the library workspace and one reduction kernel adds them in order and applies
-// alpha and beta.  The ranges run on the three-stage 128 x 128 tile (one
-// work-group per compute unit; FP64 and FP32) when that fills at least three
-// quarters of the compute units in one round, else, for FP64 only, on the chosen
-// two-stage tile with about four work-groups per compute unit (for FP32, twice as
+// alpha and beta.  The number of ranges is the one that gives the 128 x 128
+// tile one work-group per compute unit (FP64 and FP32), when that fills at least
+// three quarters of the compute units in one round, else, for FP64 only, the chosen
+// two-stage tile about four work-groups per compute unit (for FP32, twice as
 // fast per tile, that lost 4 % to the extra reduction, so FP32 then runs whole).
 constexpr int64_t SPLITK_MIN_K = 256;
 constexpr int64_t SPLITK_FIRST_K = 2048;
@@ -321,10 +321,20 @@ static SplitPlan splitk_plan(const GemmArgs &a, const KernelEntry *e, int32_t dt
 // S*m*n elements).
 int32_t launch_splitk_into(const KernelEntry *e, const GemmArgs &a, int32_t dtype,
                                   bool al, const SplitPlan &sp, uint8_t *W, hipStream_t s) {
-    hipError_t he = sp.pipe ? launch_pipe_splitk(a, dtype, sp.S, sp.kc, W, s)
-                            : e->splitk[al ? 0 : 1](a, sp.S, sp.kc, W, s);
+    bool ran = false;
+    hipError_t he = run_direct(a, dtype, sp.S, sp.kc, W, compute_units(), s, &ran);
+    if (he == hipSuccess && !ran) he = e->splitk[al ? 0 : 1](a, sp.S, sp.kc, W, s);
     if (he == hipSuccess) he = splitk_reduce(dtype, W, sp.S, a, s);
     return he == hipSuccess ? 0 : hip_error(he, "split-k launch");
+}
+
+hipError_t launch_whole(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s) {
+    if (!cp.named) {
+        bool ran = false;
+        const hipError_t he = run_direct(a, dtype, 1, a.k, nullptr, compute_units(), s, &ran);
+        if (he != hipSuccess || ran) return he;
+    }
+    return (cp.al ? cp.e->launch : cp.e->launch_unaligned)(a, s);
 }
 
 // Split-k with its planes in the library workspace (grown on demand).
@@ -336,7 +346,7 @@ static int32_t run_splitk(const KernelEntry *e, const GemmArgs &a, int32_t dtype
     });
 }
 
-// Three-stage tiles for rows that are whole 16-byte loads, each with the rate it
+// Direct-load tiles for rows that are whole 16-byte loads, each with the rate it
 // sustains while every compute unit is busy (TFLOP/s: square N = 12288 on MI355X,
 // calls back to back).  A product of T tiles of one of them runs in
 // R = ceil(T / CUs) rounds that are T / (R CUs) full; the built-in choice takes
@@ -449,6 +459,7 @@ int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg,
     const KernelEntry *e = choose_entry(dtype, a.m, a.n, cfg, &err);
     if (!e) return err;
     cp.al = rows_aligned(a.A, a.lda, a.B, a.ldb, dtype);
+    cp.named = cfg != nullptr;
     const bool in_range = in_measured_range(a.m, a.n, a.k);
     if (!cfg && (!in_range || a.k >= SPLITK_FIRST_K)) {
         // the preferred tile with k cut into ranges where that tile leaves the GPU
@@ -470,11 +481,12 @@ int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg,
             g_err.clear();     // a model that could not be used leaves the built-in choice
             if (me) {
                 cp.e = me;
+                cp.named = true;
                 return 0;
             }
         }
-        // rows the three-stage kernels load: a split tail where it pays, else the
-        // three-stage tile that fills the compute units' rounds best, where one
+        // rows of whole 16-byte loads: a split tail where it pays, else the
+        // direct-load tile that fills the compute units' rounds best, where one
         // fills them well enough
         if (rows16) {
             double best_tf = 0.0;
@@ -487,8 +499,7 @@ int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg,
             }
         }
         // the configuration measured fastest for shapes like this one: always for
-        // rows the three-stage kernels cannot load (which the preference list
-        // favours), else where the list names a two-stage configuration
+        // other rows, else where the list names a two-stage configuration
         if (in_range && (!rows16 || e->cfg.double_buffer != 2)) {
             const KernelEntry *t = measured_entry(dtype, rows16, a.m, a.n, a.k);
             if (t) e = t;
@@ -522,13 +533,13 @@ static int32_t gemm_impl(int64_t m, int64_t n, int64_t k, double alpha, const vo
     if (cp.main_rows > 0) {
         GemmArgs am = a;
         am.m = cp.main_rows;
-        hipError_t he = (cp.al ? cp.e->launch : cp.e->launch_unaligned)(am, s);
+        hipError_t he = launch_whole(cp, am, dtype, s);
         if (he != hipSuccess) return hip_error(he, "gemm launch");
         return run_splitk(cp.e, rows_from(a, cp.main_rows, elem_size(dtype)), dtype, cp.al, cp.sp,
                           s);
     }
     if (cp.sp.S > 1) return run_splitk(cp.e, a, dtype, cp.al, cp.sp, s);
-    hipError_t he = (cp.al ? cp.e->launch : cp.e->launch_unaligned)(a, s);
+    hipError_t he = launch_whole(cp, a, dtype, s);
     if (he != hipSuccess) return hip_error(he, "gemm launch");
     return 0;
 }
@@ -625,7 +636,7 @@ int32_t mgemm_choice(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, 
     *out = cp.e->cfg;
     if (main_rows) *main_rows = cp.main_rows > 0 ? cp.main_rows : (cp.sp.S > 1 ? 0 : m);
     if (cp.sp.S > 1 && cp.sp.pipe) {
-        // the three-stage 128 x 128 tile runs the ranges
+        // the ranges are counted for the direct-load 128 x 128 tile
         int cnt = 0;
         const KernelEntry *reg = registry(dtype, &cnt);
         for (int i = 0; i < cnt; ++i)

@@ -112,12 +112,15 @@ int crt_operand_bits(int64_t k);
 hipError_t crt_launch(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
                       int8_t *QA, int8_t *QB, uint8_t *R, int64_t mp, int64_t np, int64_t kp);
 
-// Split-k partials with the three-stage 128 x 128 tile, FP64 or FP32 (dtype;
-// otherwise the contract of SplitkLaunchFn); hipErrorInvalidValue unless
-// pipe_splitk_eligible.
+// Whether the plan may cut k on 128 x 128 tiles (rows of whole 16-byte loads).
 bool pipe_splitk_eligible(const GemmArgs &a, int32_t dtype);
-hipError_t launch_pipe_splitk(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void *W,
-                              hipStream_t s);
+
+// Runs an FP64 or FP32 product on the direct-load tile estimated fastest, whole (S =
+// 1, kc = k, W NULL) or as the S partial products of kc values of k each (planes of
+// W, as SplitkLaunchFn); *ran is false, and nothing runs, where no such tile can
+// load the operands.
+hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void *W, int cus,
+                      hipStream_t s, bool *ran);
 
 // C = alpha * (sum of the S partial planes of W, in plane order) + beta * C.
 hipError_t splitk_reduce(int32_t dtype, const void *W, int S, const GemmArgs &a, hipStream_t s);
@@ -132,17 +135,21 @@ int32_t with_workspace(size_t bytes, hipStream_t s, const std::function<int32_t(
 struct SplitPlan {
     int S = 1;              // number of k ranges (1: no split)
     int64_t kc = 0;         // k per range
-    bool pipe = false;      // three-stage 128 x 128 tile
+    bool pipe = false;      // counted for the direct-load 128 x 128 tile
 };
 
 // What gemm_ex runs for one FP64 or FP32 product: the kernel entry, whether A
 // and B rows take vector loads (al), and for the built-in choice the split of k.
+// The built-in choice's entry names the sum order and the split; unless the
+// configuration was named, the direct-load tile estimated fastest executes it (the
+// same bits), and the entry itself only where no direct-load tile can.
 // With main_rows > 0, rows [0, main_rows) run whole on e and only the remaining
 // rows run the split (a tail that would otherwise leave most compute units idle
 // in a last round).
 struct CallPlan {
     const KernelEntry *e = nullptr;
     bool al = false;
+    bool named = false;     // e is the caller's or the loaded model's configuration: run it
     SplitPlan sp;
     int64_t main_rows = 0;
 };
@@ -161,6 +168,8 @@ inline GemmArgs rows_from(const GemmArgs &a, int64_t r, size_t es) {
 // device only when model_may_launch, else only its cached choices count.
 int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg, bool model_may_launch,
                   CallPlan &cp);
+// A whole product (or its whole rows) of a plan, on stream s.
+hipError_t launch_whole(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s);
 // The S partial products of a split plan into W (at least S*m*n elements) and
 // their reduction into C, on stream s.
 int32_t launch_splitk_into(const KernelEntry *e, const GemmArgs &a, int32_t dtype, bool al,

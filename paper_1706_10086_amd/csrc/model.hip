@@ -22,7 +22,7 @@
 // Features of an m x n x k product of dtype d: x = [log2 m, log2 n, log2 k,
 // d == F64, d == F32, w], w = 1 where the rows of A and B are whole 16-byte loads
 // (n, lda and ldb multiples of 2 in FP64, of 4 in FP32, A and B 16-byte aligned:
-// the three-stage kernels run only then), scaled as (x - mean) / std in double and
+// the rows the direct-load configurations were measured on), scaled as (x - mean) / std in double and
 // rounded to float.  The prediction is the output with the largest value among
 // those whose dtype is d (lowest index on ties).
 #include <math.h>

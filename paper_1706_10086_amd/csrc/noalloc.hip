@@ -13,7 +13,7 @@ namespace mgemm {
 // device current, on the entry point's first call there with work to do) and only that address
 // is used from the host.  Every split-k plan of a 256-CU GPU fits: the ranges
 // times the tiles stay below 8 x 256 tiles of 64 x 64 (two-stage ranges) or at
-// most 256 tiles of 128 x 128 (three-stage ranges), i.e. below 2^23 partial
+// most 256 tiles of 128 x 128 (ranges counted for that tile), i.e. below 2^23 partial
 // elements, 64 MiB of FP64; a plan beyond that (a GPU with more compute units)
 // is refused.  Every call on a GPU shares its copy: calls that overlap on one
 // GPU (on different streams, or from several threads) race on it.
@@ -77,7 +77,7 @@ static int32_t gemm_noalloc_impl(int64_t m, int64_t n, int64_t k, double alpha, 
                              "%zu-byte maximum", need, SCRATCH_BYTES);
         GemmArgs am = a;
         am.m = cp.main_rows;
-        hipError_t he = (cp.al ? cp.e->launch : cp.e->launch_unaligned)(am, s);
+        hipError_t he = launch_whole(cp, am, dtype, s);
         if (he != hipSuccess) return hip_error(he, "gemm launch");
         return launch_splitk_into(cp.e, t, dtype, cp.al, cp.sp, W, s);
     }
@@ -89,7 +89,7 @@ static int32_t gemm_noalloc_impl(int64_t m, int64_t n, int64_t k, double alpha, 
                              "%zu-byte maximum", need, SCRATCH_BYTES);
         return launch_splitk_into(cp.e, a, dtype, cp.al, cp.sp, W, s);
     }
-    hipError_t he = (cp.al ? cp.e->launch : cp.e->launch_unaligned)(a, s);
+    hipError_t he = launch_whole(cp, a, dtype, s);
     if (he != hipSuccess) return hip_error(he, "gemm launch");
     return 0;
 }
