@@ -209,9 +209,12 @@ MGEMM_API int32_t gemm_batched(int64_t count, const int64_t *m, const int64_t *n
 /* Builds a reusable plan for one batched launch: problems are grouped by tile
  * configuration (cfgs[i], argument 14: a registered configuration with the
  * MGEMM_CFG_BATCHED flag, else -14; when cfgs is NULL every problem uses the
- * registered 64x64x16 four-wave configuration); per group one persistent kernel takes C
- * tiles from per-XCD atomic work lists, each tile running the code path of its
- * problem's row alignment; all groups are captured into one HIP graph.  The plan keeps the problem
+ * registered 64x64x16 four-wave configuration).  With cfgs, per group one persistent
+ * kernel takes C tiles from per-XCD atomic work lists, each tile running the code path
+ * of its problem's row alignment; without, one work-group per tile runs 64 x 64
+ * direct-load tiles dealt to the XCDs at plan time (problems whose operands those
+ * cannot load, see double_buffer, in the persistent kernel); all groups are captured
+ * into one HIP graph.  The plan keeps the problem
  * descriptors (pointers, sizes, alpha, beta) -- the matrices must stay valid and
  * are read at each execution.  Problems with k == 0 or alpha == 0 are rejected
  * (MGEMM_ERR_PLAN).  stream: the stream executions run on (NULL: null stream).

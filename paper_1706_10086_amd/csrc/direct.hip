@@ -116,4 +116,49 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
     return best ? best->launch(a, S, kc, W, s) : hipSuccess;
 }
 
+// ---------------------------------------------------------------------------
+// Many products in one launch (the default batched plan).
+// ---------------------------------------------------------------------------
+// Work-group b runs entry b / BATCH_LISTS of list b % BATCH_LISTS of the tile map (the
+// hardware deals consecutive work-groups to the XCDs in turn, so a list's tiles share
+// the panels of A and B in one L2); the hardware replaces a finished work-group by the
+// next one, so short tiles need no queue of their own.
+//
+// Bound: the matrix cores for the large products, the load latency of a tile's first
+// k-steps for the small ones, which four work-groups per compute unit hide.
+template <typename T, int BM, int BN, int BK, int OCC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC)))
+gemm_batched_direct_kernel(const BatchProblem *__restrict__ probs,
+                           const uint64_t *__restrict__ map, const int64_t *__restrict__ off) {
+    typedef PipeShape<T, BM, BN, BK, 2, 2> S;
+    __shared__ u32x4_t lds[2 * S::STAGE];
+    const unsigned list = blockIdx.x % BATCH_LISTS;
+    const int64_t idx = off[list] + (int64_t)(blockIdx.x / BATCH_LISTS);
+    if (idx >= off[list + 1]) return;
+    const uint64_t e = map[idx];
+    constexpr uint64_t RC = (1ull << TILE_MAP_RC_BITS) - 1;
+    const int64_t tm = (int64_t)((e >> TILE_MAP_RC_BITS) & RC), tn = (int64_t)(e & RC);
+    const GemmArgs g = probs[e >> (2 * TILE_MAP_RC_BITS)].g;
+    pipe_tile<T, BM, BN, BK, 2, 2, 2>(g, lds, tm * BM, tn * BN);
+}
+
+bool batched_direct_eligible(const GemmArgs &a, int32_t dtype) {
+    return dtype == MGEMM_F32 ? pipe_eligible<float, 64, 64, 32>(a)
+                              : pipe_eligible<double, 64, 64, 16>(a);
+}
+
+hipError_t launch_batched_direct(int32_t dtype, const BatchProblem *probs, const uint64_t *map,
+                                 const int64_t *off, int64_t longest, hipStream_t s) {
+    const int64_t blocks = longest * BATCH_LISTS;
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    if (dtype == MGEMM_F32)
+        hipLaunchKernelGGL((gemm_batched_direct_kernel<float, 64, 64, 32, 3>),
+                           dim3((unsigned)blocks), dim3(256), 0, s, probs, map, off);
+    else
+        hipLaunchKernelGGL((gemm_batched_direct_kernel<double, 64, 64, 16, 4>),
+                           dim3((unsigned)blocks), dim3(256), 0, s, probs, map, off);
+    return hipGetLastError();
+}
+
 }  // namespace mgemm

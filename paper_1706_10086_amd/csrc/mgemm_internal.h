@@ -122,6 +122,13 @@ bool pipe_splitk_eligible(const GemmArgs &a, int32_t dtype);
 hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void *W, int cus,
                       hipStream_t s, bool *ran);
 
+// The default batched plan's kernel: 64 x 64 direct-load tiles, work-group b taking
+// entry b / BATCH_LISTS of list b % BATCH_LISTS of the tile map (`longest`: entries of
+// the longest list).
+bool batched_direct_eligible(const GemmArgs &a, int32_t dtype);
+hipError_t launch_batched_direct(int32_t dtype, const BatchProblem *probs, const uint64_t *map,
+                                 const int64_t *off, int64_t longest, hipStream_t s);
+
 // C = alpha * (sum of the S partial planes of W, in plane order) + beta * C.
 hipError_t splitk_reduce(int32_t dtype, const void *W, int S, const GemmArgs &a, hipStream_t s);
 

@@ -59,13 +59,15 @@ inline bool pipe_eligible(const GemmArgs &a) {
 //
 // Rows and columns need no alignment beyond 4 bytes (16-byte loads at 4-byte
 // aligned addresses ran at the rate of aligned ones: 56-59 bytes per cycle and
-// compute unit either way).  The last column tile of a wide product starts at
-// n - BN instead of overhanging (its first columns repeat the neighbour's and are
-// not stored); rows >= m and, where n < BN, columns past n load clamped addresses
-// whose products are not stored.  A partial last k-step is loaded element-wise and
-// zero-padded after the loop.  Where n < BN and n is no multiple of the unit, the
-// unit at the row's end also reads the first elements of the next row, so the last
-// row of B stays with the element-wise step.
+// compute unit either way).  An overhanging column tile starts up to three columns
+// earlier, so that its last 16-byte unit ends with the row (the columns before c0
+// repeat the neighbour's and are not stored); rows >= m and units past n load
+// clamped addresses whose products are not stored, and a wave whose whole part lies
+// outside C runs no products.  A partial last k-step is loaded element-wise and
+// zero-padded after the loop.  Where n < BN and n is no multiple of the unit (the
+// first column tile cannot start earlier), the unit at the row's end also reads the
+// first elements of the next row, so the last row of B stays with the element-wise
+// step.
 //
 // The function ends with a barrier-free epilogue: a caller that reuses lds puts a
 // barrier before the next tile.
@@ -84,10 +86,14 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
     const AS_GLOBAL T *__restrict__ A = (const AS_GLOBAL T *)p.A;
     const AS_GLOBAL T *__restrict__ B = (const AS_GLOBAL T *)p.B;
     const int64_t lda = p.lda, ldb = p.ldb;
-    // columns: the tile covers [n0, n0 + BN) and stores those from c0 on
-    const int64_t n0 = p.n >= BN && c0 > p.n - BN ? p.n - BN : c0;
+    // columns: the tile covers [n0, n0 + BN) and stores those from c0 on; an
+    // overhanging tile starts up to a unit earlier, so that units end with the row
+    const int first_col =
+        c0 > 0 && p.n - c0 < BN ? (int)((S::EPU - (p.n - c0) % S::EPU) % S::EPU) : 0;
+    const int64_t n0 = c0 - first_col;
     const int64_t mrem = p.m - m0, nrem = p.n - n0;
-    const int first_col = (int)(c0 - n0);
+    // whether any row and column of this wave's part lie inside C (uniform)
+    const bool live = mrem > wm * S::WM && nrem > wn * S::WN;
 
     // Per-lane source byte offsets of each load instruction, relative to the
     // tile's A panel (A + m0*lda) or B panel (B + n0) at k-step 0.
@@ -199,7 +205,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
 
     // full k-steps; the rest (a partial last k-step, or a whole one whose last row
     // of B the direct loads must not take) is loaded element-wise
-    const bool row_end = nrem < BN && p.n % S::EPU != 0;
+    const bool row_end = nrem < BN && nrem % S::EPU != 0;
     const int64_t nk = row_end ? (p.k - 1) / BK : p.k / BK;
     const int ktail = (int)(p.k - nk * BK);
     if (nk > 0) {
@@ -223,7 +229,9 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
             wait_steps(std::integral_constant<int, NST - 2>());
             __syncthreads();
             const int st1 = st == NST - 1 ? 0 : st + 1;
-            products(lds + st1 * S::STAGE, c + NST < nk ? c + NST : nk - 1, lds + st * S::STAGE);
+            const int64_t ahead = c + NST < nk ? c + NST : nk - 1;
+            if (live) products(lds + st1 * S::STAGE, ahead, lds + st * S::STAGE);
+            else issue(ahead, lds + st * S::STAGE);
             st = st1;
         }
         wait_steps(std::integral_constant<int, 0>());    // no load may land after this point
@@ -259,6 +267,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
             sT[S::A_UNITS * S::EPU + (tid + e * S::NT) / BN * S::BU * S::EPU +
                (tid + e * S::NT) % BN] = tb[e];
         __syncthreads();
+        if (!live) return;
 #pragma unroll
         for (int g = 0; g < S::G; ++g) {
 #pragma unroll
@@ -276,6 +285,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
         }
     }
 
+    if (!live) return;
     // Epilogue: lane holds column l16 and rows E::out_row(kq, 0..3) of each fragment.
     // The C loads of one fragment row go out together before its stores; on edge
     // tiles they read clamped addresses and the stores are tested.

@@ -90,3 +90,33 @@ def test_direct_tiles_long_k(dev, dtype, shape):
     # the reference's own rounding adds its gamma with the FP64 unit
     bound = (gam(u) + gam(2.0 ** -53)) * (1.5 * np.abs(A64) @ np.abs(B64) + 0.5 * np.abs(C64))
     assert np.all(err <= bound)
+
+
+@pytest.mark.parametrize("dtype", [mg.F64, mg.F32])
+def test_default_plan_mixes_direct_and_register_staged(dev, dtype):
+    """A plan without configurations: problems the direct loads take (any alignment)
+    beside rows of fewer elements than one load unit, which they cannot; bit for bit
+    the 64 x 64 x 16 configuration per problem, in one configuration group."""
+    tdt = torch.float64 if dtype == mg.F64 else torch.float32
+    g = torch.Generator(device=dev)
+    g.manual_seed(17)
+    shapes = [(m, n, k, (m + n) % 3, k % 2, n % 2, m % 4) for m, n, k in
+              [(1, 1, 1), (70, 1, 33), (65, 2, 64), (20, 3, 17), (129, 5, 40), (64, 64, 48),
+               (63, 65, 1), (200, 333, 77), (333, 200, 130), (17, 1000, 5), (1000, 17, 250)]]
+    As = [embedded(m, k, pa, oa, tdt, dev, g)[1] for m, n, k, pa, pb, oa, ob in shapes]
+    Bs = [embedded(k, n, pb, ob, tdt, dev, g)[1] for m, n, k, pa, pb, oa, ob in shapes]
+    Cs = [embedded(m, n, pa, ob, tdt, dev, g)[1] for m, n, k, pa, pb, oa, ob in shapes]
+    want = [c.clone() for c in Cs]
+    cfg = [c for c in mg.configs(dtype) if c.as_tuple() == (64, 64, 16, 4, 2, 1, 0)][0]
+    plan = mg.BatchedPlan(As, Bs, Cs, 1.25, -0.5)
+    info = plan.info()
+    assert info["buckets"] == 1
+    assert info["tiles"] == sum(-(-m // 64) * -(-n // 64) for m, n, *_ in shapes)
+    plan.execute()
+    for a, b, c in zip(As, Bs, want):
+        mg.gemm(a, b, c, 1.25, -0.5, cfg=cfg)
+    torch.cuda.synchronize()
+    for s, c, w in zip(shapes, Cs, want):
+        print(f"default plan dtype={mg.DTYPE_NAMES[dtype]} {s}", flush=True)
+        assert torch.equal(c, w), s
+    plan.destroy()
