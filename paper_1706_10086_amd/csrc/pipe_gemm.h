@@ -64,10 +64,10 @@ inline bool pipe_eligible(const GemmArgs &a) {
 // repeat the neighbour's and are not stored); rows >= m and units past n load
 // clamped addresses whose products are not stored, and a wave whose whole part lies
 // outside C runs no products.  A partial last k-step is loaded element-wise and
-// zero-padded after the loop.  Where n < BN and n is no multiple of the unit (the
-// first column tile cannot start earlier), the unit at the row's end also reads the
-// first elements of the next row, so the last row of B stays with the element-wise
-// step.
+// zero-padded.  Where n < BN and n is no
+// multiple of the unit (the first column tile cannot start earlier), the unit at the
+// row's end also reads the first elements of the next row, so the last row of B stays
+// with the element-wise step.
 //
 // The function ends with a barrier-free epilogue: a caller that reuses lds puts a
 // barrier before the next tile.
@@ -96,25 +96,28 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
     const bool live = mrem > wm * S::WM && nrem > wn * S::WN;
 
     // Per-lane source byte offsets of each load instruction, relative to the
-    // tile's A panel (A + m0*lda) or B panel (B + n0) at k-step 0.
+    // tile's A panel (A + m0*lda) or B panel (B + n0) at k-step 0 (32 bits:
+    // pipe_eligible).
+    const int mlast = mrem < BM ? (int)mrem - 1 : BM - 1;
+    const int nlast = nrem < BN ? (int)nrem : BN;
+    const uint32_t lda_b = (uint32_t)(lda * (int64_t)sizeof(T));
+    const uint32_t ldb_b = (uint32_t)(ldb * (int64_t)sizeof(T));
     uint32_t src_off[S::LOADS];
 #pragma unroll
     for (int i = 0; i < S::LOADS; ++i) {
-        const int u = i * S::NT + wave * 64 + lane;
-        int64_t e;
+        const int u = i * S::NT + tid;
         if (u < S::A_UNITS) {
             const int r = u / S::AU, c = u % S::AU;
-            const int64_t row = r < mrem ? r : mrem - 1;
-            e = (row < BM ? row : BM - 1) * lda + (c < S::ROW_A ? c : S::ROW_A - 1) * S::EPU;
+            src_off[i] = (uint32_t)(r < mlast ? r : mlast) * lda_b +
+                         (uint32_t)(c < S::ROW_A ? c : S::ROW_A - 1) * 16u;
         } else {
             const int v = u - S::A_UNITS;
             const int r = v / S::BU, c = v % S::BU;
-            int64_t col = (int64_t)(c < S::ROW_B ? c : S::ROW_B - 1) * S::EPU;
+            int col = (c < S::ROW_B ? c : S::ROW_B - 1) * S::EPU;
             // a unit wholly past n reads the row's last whole unit instead
-            if (col >= nrem) col = nrem - S::EPU;
-            e = (int64_t)(r < BK ? r : BK - 1) * ldb + col;
+            if (col >= nlast) col = nlast - S::EPU;
+            src_off[i] = (uint32_t)(r < BK ? r : BK - 1) * ldb_b + (uint32_t)col * (uint32_t)sizeof(T);
         }
-        src_off[i] = (uint32_t)(e * (int64_t)sizeof(T));
     }
     const AS_GLOBAL char *Apanel = (const AS_GLOBAL char *)(A + m0 * lda);
     const AS_GLOBAL char *Bpanel = (const AS_GLOBAL char *)(B + n0);
@@ -168,12 +171,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
         for (int j = 0; j < S::FN; ++j)
             bf[g][h][j] = stT[b_elem + (g * 8 + h) * S::BU * S::EPU + j * 16];
     };
-    // products of one k-step; each fragment is refilled from the next stage right
-    // after its last use (past the last k-step the refills read a stale stage and
-    // are never used).  The loads of k-step lk into stage lst are spread over the
-    // products, one every few fragment rows, so the memory pipeline takes a few at a
-    // time instead of every wave queueing all of them at the barrier.
-    auto products = [&](const u32x4_t *nst, int64_t lk, u32x4_t *lst) {
+    // products of one k-step; with REFILL each fragment is refilled from the next
+    // stage right after its last use.  With LOAD the loads of k-step lk into stage
+    // lst are spread over the products, one every few fragment rows, so the memory
+    // pipeline takes a few at a time instead of every wave queueing all of them at
+    // the barrier.
+    auto products = [&](auto load, auto refill, const u32x4_t *nst, int64_t lk, u32x4_t *lst) {
+        constexpr bool LOAD = decltype(load)::value, REFILL = decltype(refill)::value;
         constexpr int SLOTS = S::G * 2 * S::FM;
         constexpr int EVERY = SLOTS / S::LOADS > 0 ? SLOTS / S::LOADS : 1;
         constexpr int PER = (S::LOADS + SLOTS - 1) / SLOTS;        // loads per slot
@@ -187,9 +191,9 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
 #pragma unroll
                     for (int j = 0; j < S::FN; ++j)
                         acc[i][j] = E::mma(af[g][i][h], bf[g][h][j], acc[i][j]);
-                    if (h == 1) read_a(nst, g, i);
+                    if (REFILL && h == 1) read_a(nst, g, i);
                     const int slot = (g * 2 + h) * S::FM + i;
-                    if (slot % EVERY == 0) {
+                    if (LOAD && slot % EVERY == 0) {
 #pragma unroll
                         for (int q = 0; q < PER; ++q)
                             if (slot / EVERY * PER + q < S::LOADS)
@@ -197,68 +201,47 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
                     }
                     if (h == 1 || slot % EVERY == 0) __builtin_amdgcn_sched_barrier(0);
                 }
-                read_b(nst, g, h);
+                if (REFILL) read_b(nst, g, h);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
 
-    // full k-steps; the rest (a partial last k-step, or a whole one whose last row
-    // of B the direct loads must not take) is loaded element-wise
+    // k-steps: nk full ones by direct loads; the rest (a partial last k-step, or a
+    // whole one whose last row of B the direct loads must not take) element by
+    // element, zero outside A and B (as the two-stage kernel pads)
     const bool row_end = nrem < BN && nrem % S::EPU != 0;
     const int64_t nk = row_end ? (p.k - 1) / BK : p.k / BK;
     const int ktail = (int)(p.k - nk * BK);
-    if (nk > 0) {
-#pragma unroll
-        for (int c = 0; c < NST; ++c) issue(c < nk ? c : nk - 1, lds + c * S::STAGE);
-        wait_steps(std::integral_constant<int, NST - 1>());
-        __syncthreads();
-#pragma unroll
-        for (int g = 0; g < S::G; ++g) {
-#pragma unroll
-            for (int i = 0; i < S::FM; ++i) read_a(lds, g, i);
-            read_b(lds, g, 0);
-            read_b(lds, g, 1);
-        }
-        // Past the end the loads repeat the last k-step (in bounds, never used),
-        // which keeps the loop free of branches around the products.
-        int st = 0;
-        for (int64_t c = 0; c < nk; ++c) {
-            // own loads of k-step c+1 landed, then everyone's; every wave holds
-            // k-step c in registers
-            wait_steps(std::integral_constant<int, NST - 2>());
-            __syncthreads();
-            const int st1 = st == NST - 1 ? 0 : st + 1;
-            const int64_t ahead = c + NST < nk ? c + NST : nk - 1;
-            if (live) products(lds + st1 * S::STAGE, ahead, lds + st * S::STAGE);
-            else issue(ahead, lds + st * S::STAGE);
-            st = st1;
-        }
-        wait_steps(std::integral_constant<int, 0>());    // no load may land after this point
-    }
-    if (ktail) {
-        // The last k-step: element-wise loads, zero outside A and B (as the two-stage
-        // kernel pads), into stage 0 once every wave is done with LDS.
-        __syncthreads();
-        const int64_t k0 = nk * BK;
-        T *sT = (T *)lds;
-        constexpr int NA = BM * BK / S::NT, NB = BK * BN / S::NT;
-        static_assert(NA * S::NT == BM * BK && NB * S::NT == BK * BN, "tail split");
-        T ta[NA], tb[NB];
+    constexpr int NA = BM * BK / S::NT, NB = BK * BN / S::NT;
+    static_assert(NA * S::NT == BM * BK && NB * S::NT == BK * BN, "tail split");
+    // Where 16 registers hold a thread's share of that step, it is loaded before the
+    // loop, its latency hidden behind the full k-steps, and takes its stage within
+    // the loop; for the larger tiles (which have no registers to spare: FP64 128 x 128
+    // x 16 spilled) it follows the loop.
+    constexpr bool EARLY_TAIL = (NA + NB) * (int)sizeof(T) <= 64;
+    const int64_t steps = nk + (EARLY_TAIL && ktail ? 1 : 0);
+    T ta[NA], tb[NB];
+    auto load_tail = [&]() {
+        const AS_GLOBAL T *At = (const AS_GLOBAL T *)(Apanel + nk * (BK * (int64_t)sizeof(T)));
+        const AS_GLOBAL T *Bt = (const AS_GLOBAL T *)(Bpanel + nk * (BK * ldb * (int64_t)sizeof(T)));
 #pragma unroll
         for (int e = 0; e < NA; ++e) {
             const int r = (tid + e * S::NT) / BK, c = (tid + e * S::NT) % BK;
-            const bool in = r < mrem && c < ktail;
-            ta[e] = A[(m0 + (in ? r : 0)) * lda + k0 + (in ? c : 0)];
+            const bool in = r <= mlast && c < ktail;
+            ta[e] = At[(int64_t)(in ? r : 0) * lda + (in ? c : 0)];
             if (!in) ta[e] = (T)0;
         }
 #pragma unroll
         for (int e = 0; e < NB; ++e) {
             const int r = (tid + e * S::NT) / BN, c = (tid + e * S::NT) % BN;
-            const bool in = r < ktail && c < nrem;
-            tb[e] = B[(k0 + (in ? r : 0)) * ldb + n0 + (in ? c : 0)];
+            const bool in = r < ktail && c < nlast;
+            tb[e] = Bt[(int64_t)(in ? r : 0) * ldb + (in ? c : 0)];
             if (!in) tb[e] = (T)0;
         }
+    };
+    auto store_tail = [&](u32x4_t *stage) {
+        T *sT = (T *)stage;
 #pragma unroll
         for (int e = 0; e < NA; ++e)
             sT[(tid + e * S::NT) / BK * S::AU * S::EPU + (tid + e * S::NT) % BK] = ta[e];
@@ -266,22 +249,74 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
         for (int e = 0; e < NB; ++e)
             sT[S::A_UNITS * S::EPU + (tid + e * S::NT) / BN * S::BU * S::EPU +
                (tid + e * S::NT) % BN] = tb[e];
-        __syncthreads();
-        if (!live) return;
+    };
+
+    // k-step c sits in stage c % NST; the first NST are filled here
+#pragma unroll
+    for (int c = 0; c < NST; ++c)
+        if (c < nk) issue(c, lds + c * S::STAGE);
+    if (EARLY_TAIL && ktail) load_tail();
+    if (EARLY_TAIL && nk < NST && ktail) store_tail(lds + (int)nk * S::STAGE);
+    // (the count is of the newest loads: any others among them only make it wait longer)
+    if (nk >= NST) wait_steps(std::integral_constant<int, NST - 1>());
+    else wait_steps(std::integral_constant<int, 0>());
+    __syncthreads();
+    if (live) {
 #pragma unroll
         for (int g = 0; g < S::G; ++g) {
 #pragma unroll
             for (int i = 0; i < S::FM; ++i) read_a(lds, g, i);
             read_b(lds, g, 0);
             read_b(lds, g, 1);
+        }
+    }
+    int st = 0;
+    int64_t c = 0;
+    // while full k-steps are left to load: own loads of k-step c+1 landed, then
+    // everyone's; every wave holds k-step c in registers
+    for (; c + NST < nk; ++c) {
+        wait_steps(std::integral_constant<int, NST - 2>());
+        __syncthreads();
+        const int st1 = st == NST - 1 ? 0 : st + 1;
+        if (live)
+            products(std::true_type(), std::true_type(), lds + st1 * S::STAGE, c + NST,
+                     lds + st * S::STAGE);
+        else
+            issue(c + NST, lds + st * S::STAGE);
+        st = st1;
+    }
+    // the rest: the element-wise k-step takes the stage that k-step nk - NST left
+#pragma unroll 1
+    for (; c < steps; ++c) {
+        wait_steps(std::integral_constant<int, 0>());
+        __syncthreads();
+        const int st1 = st == NST - 1 ? 0 : st + 1;
+        if (EARLY_TAIL && ktail && c + NST == nk) store_tail(lds + st * S::STAGE);
+        if (live)
+            products(std::false_type(), std::true_type(), lds + st1 * S::STAGE, 0, lds);
+        st = st1;
+    }
+    if (!EARLY_TAIL && ktail) {
+        load_tail();
+        __syncthreads();                 // every wave is done with LDS
+        store_tail(lds);
+        __syncthreads();
+        if (live) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int g = 0; g < S::G; ++g) {
 #pragma unroll
-                for (int i = 0; i < S::FM; ++i)
+                for (int i = 0; i < S::FM; ++i) read_a(lds, g, i);
+                read_b(lds, g, 0);
+                read_b(lds, g, 1);
 #pragma unroll
-                    for (int j = 0; j < S::FN; ++j)
-                        acc[i][j] = E::mma(af[g][i][h], bf[g][h][j], acc[i][j]);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < S::FN; ++j)
+                            acc[i][j] = E::mma(af[g][i][h], bf[g][h][j], acc[i][j]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 
