@@ -6,17 +6,18 @@
 //   Adam update of all parameters (Kingma and Ba, ICLR 2015, Algorithm 1)
 //
 // Parameters are one flat FP32 vector W1, b1, W2, b2, W3, b3 (row-major).  The
-// training set (rows of x, targets t, mask M) lives on the device; one training
-// step (forward, loss, backward, Adam) is captured once into a HIP graph and
-// replayed per step.  The linear layers' products (forward, the backward
-// products and the weight gradients) run on the matrix cores in FP32; every
-// reduction runs in a fixed order, so training is deterministic.
+// training set (rows of x, targets t, mask M) lives on the device.  Networks of at
+// most 32 inputs and 128 hidden units train with two kernels a step (mlp_step.h);
+// for wider ones a step (forward, loss, backward, Adam) runs layer by layer, captured
+// once into a HIP graph and replayed per step.  The linear layers' products (forward,
+// the backward products and the weight gradients) run on the matrix cores in FP32;
+// every reduction runs in a fixed order, so training is deterministic.
 #include <math.h>
 
 #include <algorithm>
 #include <vector>
 
-#include "tile_gemm.h"
+#include "mlp_step.h"
 
 namespace mgemm {
 
@@ -301,6 +302,7 @@ struct Mlp {
     float *z1 = nullptr, *h1 = nullptr, *z2 = nullptr, *h2 = nullptr, *y = nullptr;
     float *d = nullptr, *dz2 = nullptr, *dz1 = nullptr;   // d = M (y - t)
     float *planes = nullptr;  // partial gradient planes
+    int blocks = 0;           // > 0: the step kernel trains, with this many blocks
     float *part = nullptr;    // per-tile loss sums of the output layer
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
@@ -335,6 +337,34 @@ static void free_data(Mlp *p) {
     p->exec = nullptr;
     p->graph = nullptr;
     p->B = 0;
+    p->blocks = 0;
+}
+
+// Blocks of the step kernel for a training set of `rows` rows (0: the network is too
+// wide for it): one per tile of rows, at most one per compute unit.
+static int step_rows(const Mlp *p) { return p->H <= 64 ? 64 : 32; }
+
+static int step_blocks(const Mlp *p, int64_t rows) {
+    if (p->I > STEP_MAX_IN || p->H > STEP_MAX_HIDDEN) return 0;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        cus = 256;
+    return (int)std::min<int64_t>((rows + step_rows(p) - 1) / step_rows(p), cus);
+}
+
+// Loss and gradient of one step on the step kernel, and with lr > 0 Adam's update.
+static void step_launch(Mlp *p, hipStream_t s, float lr, float b1, float b2, float eps) {
+    const MlpStepArgs a{p->I, p->H, p->O, p->B, p->X, p->T, p->M, p->par, p->planes, p->part,
+                        lr > 0.0f ? p->step : (int *)nullptr};
+    if (step_rows(p) == 64)
+        hipLaunchKernelGGL((mlp_step_kernel<64, 64>), dim3(p->blocks), dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((mlp_step_kernel<128, 32>), dim3(p->blocks), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(mlp_update_kernel, dim3((unsigned)((p->P + 31) / 32)), dim3(256), 0, s,
+                       p->planes, p->blocks, p->P, p->part, p->loss, p->grad, p->par, p->m, p->v,
+                       lr, b1, b2, eps, (const int *)p->step);
 }
 
 static dim3 mm_grid(int M, int N, int S) {
@@ -538,12 +568,19 @@ int32_t mlp_set_data(void *handle, int64_t rows, const float *X, const float *T,
     const int64_t B = rows;
     const int64_t tiles3 = ((B + MM_T - 1) / MM_T) * ((p->O + MM_T - 1) / MM_T);
     p->B = B;    // for planes_elems; reset below on failure
+    const int blocks = step_blocks(p, B);
+    p->blocks = blocks;
+    const bool whole = blocks == 0;     // the step kernel keeps no activations
     struct { float **dst; int64_t n; } bufs[] = {
-        {&p->X, B * p->I}, {&p->T, B * p->O}, {&p->M, B * p->O}, {&p->z1, B * p->H},
-        {&p->h1, B * p->H}, {&p->z2, B * p->H}, {&p->h2, B * p->H}, {&p->y, B * p->O},
-        {&p->d, B * p->O}, {&p->dz2, B * p->H}, {&p->dz1, B * p->H},
-        {&p->planes, planes_elems(p, B)}, {&p->part, 2 * tiles3}};
+        {&p->X, B * p->I}, {&p->T, B * p->O}, {&p->M, B * p->O}, {&p->z1, whole ? B * p->H : 0},
+        {&p->h1, whole ? B * p->H : 0}, {&p->z2, whole ? B * p->H : 0},
+        {&p->h2, whole ? B * p->H : 0}, {&p->y, whole ? B * p->O : 0},
+        {&p->d, whole ? B * p->O : 0}, {&p->dz2, whole ? B * p->H : 0},
+        {&p->dz1, whole ? B * p->H : 0},
+        {&p->planes, whole ? planes_elems(p, B) : blocks * p->P},
+        {&p->part, whole ? 2 * tiles3 : 2 * (int64_t)blocks}};
     for (auto &b : bufs) {
+        if (b.n == 0) continue;
         if (hipMalloc((void **)b.dst, (size_t)b.n * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             *b.dst = nullptr;
@@ -566,7 +603,8 @@ int32_t mlp_loss_grad(void *handle, float *loss, float *grad) {
     if (!p) return set_error(-1, "handle is NULL");
     if (p->B == 0) return set_error(MGEMM_ERR_PLAN, "mlp: no training data");
     hipStream_t s = current_stream();
-    mlp_grad_launch(p, s, false);
+    if (p->blocks) step_launch(p, s, 0.0f, 0.0f, 0.0f, 0.0f);
+    else mlp_grad_launch(p, s, false);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess && loss) e = hipMemcpy(loss, p->loss, sizeof(float), hipMemcpyDeviceToHost);
@@ -587,6 +625,17 @@ int32_t mlp_train(void *handle, int32_t steps, float lr, float beta1, float beta
     if (p->B == 0) return set_error(MGEMM_ERR_PLAN, "mlp: no training data");
     hipStream_t s = current_stream();
     hipError_t e = hipSuccess;
+    if (p->blocks) {
+        // two kernels a step: their launches take less time than their work
+        for (int i = 0; i < steps && e == hipSuccess; ++i) {
+            step_launch(p, s, lr, beta1, beta2, eps);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e == hipSuccess && last_loss)
+            e = hipMemcpy(last_loss, p->loss, sizeof(float), hipMemcpyDeviceToHost);
+        return e == hipSuccess ? 0 : hip_err(e, "mlp_train");
+    }
     // one training step, captured once per hyper-parameter set
     if (!p->exec || p->g_lr != lr || p->g_b1 != beta1 || p->g_b2 != beta2 || p->g_eps != eps) {
         if (p->exec) (void)hipGraphExecDestroy(p->exec);
