@@ -197,7 +197,9 @@ MGEMM_API int32_t gemm_ex_noalloc(int64_t m, int64_t n, int64_t k, double alpha,
  * problem returns that argument's -i code and names the problem in
  * mgemm_last_error).
  *
- * gemm_batched: one gemm launch per problem, in order, on the current stream.
+ * gemm_batched: gemm's result for every problem, as if called in order, on the
+ * current stream; small problems (MGEMM_F64, MGEMM_F32) that neither read nor rewrite
+ * what others of the list write share launches.
  * Array arguments are numbered 2..12 after count (1); dtype is 13.
  */
 MGEMM_API int32_t gemm_batched(int64_t count, const int64_t *m, const int64_t *n,
@@ -271,7 +273,8 @@ MGEMM_API int32_t mlp_set_data(void *mlp, int64_t rows, const float *X, const fl
 /* Loss and gradient (host outputs, either may be NULL) on the training set,
  * without an update. */
 MGEMM_API int32_t mlp_loss_grad(void *mlp, float *loss, float *grad);
-/* steps full-batch Adam steps (one captured HIP graph per step); *last_loss
+/* steps full-batch Adam steps (two kernels per step for networks of at most 32
+ * inputs and 128 hidden units, else one captured HIP graph per step); *last_loss
  * (host, may be NULL) receives the loss evaluated in the last step. */
 MGEMM_API int32_t mlp_train(void *mlp, int32_t steps, float lr, float beta1, float beta2,
                             float eps, float *last_loss);

@@ -50,6 +50,58 @@ static hipError_t launch_direct(const GemmArgs &a, int S, int64_t kc, void *W, h
     return hipGetLastError();
 }
 
+// Several whole products in one launch, described in the kernel's arguments (no copy
+// to the device, nothing kept between calls): work-group b runs a tile of the problem
+// whose tiles start at or before b.
+constexpr int LIST_MAX = 56;                  // arguments below 4 KiB
+
+struct ListProblem {
+    const void *A, *B;
+    void *C;
+    double alpha, beta;
+    int32_t m, n, k, lda, ldb, ldc;
+};
+
+struct ListArgs {
+    int32_t count;
+    int32_t first[LIST_MAX];                  // first tile of each problem
+    ListProblem p[LIST_MAX];
+};
+
+template <typename T, int BM, int BN, int BK, int OCC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC)))
+gemm_list_kernel(ListArgs a) {
+    typedef PipeShape<T, BM, BN, BK, 2, 2> S;
+    static_assert(LIST_MAX <= 64, "one lane per problem");
+    __shared__ u32x4_t lds[2 * S::STAGE];
+    const int lane = threadIdx.x & 63, bid = (int)blockIdx.x;
+    const bool at = lane < a.count && a.first[lane < LIST_MAX ? lane : 0] <= bid;
+    const int pi = __builtin_amdgcn_readfirstlane(__popcll(__ballot(at)) - 1);
+    const ListProblem &q = a.p[pi];
+    const int tiles_n = (q.n + BN - 1) / BN, local = bid - a.first[pi];
+    const int tm = local / tiles_n, tn = local - tm * tiles_n;
+    const GemmArgs g{q.m, q.n, q.k, q.alpha, q.beta, q.A, q.lda, q.B, q.ldb, q.C, q.ldc};
+    pipe_tile<T, BM, BN, BK, 2, 2, 2>(g, lds, (int64_t)tm * BM, (int64_t)tn * BN);
+}
+
+template <typename T, int BM, int BN, int BK, int OCC>
+static hipError_t launch_list(const GemmArgs *p, int count, hipStream_t s) {
+    ListArgs a;
+    a.count = count;
+    int64_t tiles = 0;
+    for (int i = 0; i < count; ++i) {
+        const GemmArgs &g = p[i];
+        a.first[i] = (int32_t)tiles;
+        a.p[i] = {g.A, g.B, g.C, g.alpha, g.beta, (int32_t)g.m, (int32_t)g.n, (int32_t)g.k,
+                  (int32_t)g.lda, (int32_t)g.ldb, (int32_t)g.ldc};
+        tiles += ((g.m + BM - 1) / BM) * ((g.n + BN - 1) / BN);
+    }
+    if (tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((gemm_list_kernel<T, BM, BN, BK, OCC>), dim3((unsigned)tiles), dim3(256), 0,
+                       s, a);
+    return hipGetLastError();
+}
+
 // A tile and its time: with q = ceil(tiles / CUs) work-groups for the busiest
 // compute unit, R of them at a time, and k rounded up to the k-step,
 //   t = start + each q + rate k (BM BN / 4096) (sum over rounds of (alone + r))
@@ -65,10 +117,12 @@ struct DirectTile {
     double start, each, rate, alone;
     hipError_t (*launch)(const GemmArgs &, int, int64_t, void *, hipStream_t);
     bool (*eligible)(const GemmArgs &);
+    hipError_t (*list)(const GemmArgs *, int, hipStream_t);
 };
 
 #define DIRECT(T, BM, BN, BK, OCC, R, START, EACH, RATE, ALONE) \
-    {BM, BN, BK, R, START, EACH, RATE, ALONE, &launch_direct<T, BM, BN, BK, OCC>, &pipe_eligible<T, BM, BN, BK>}
+    {BM, BN, BK, R, START, EACH, RATE, ALONE, &launch_direct<T, BM, BN, BK, OCC>, &pipe_eligible<T, BM, BN, BK>, \
+     &launch_list<T, BM, BN, BK, OCC>}
 
 static const DirectTile kDirectF64[] = {
     DIRECT(double, 128, 128, 16, 2, 2, 0.00, 9.90, 0.02724, 0.081),
@@ -114,6 +168,54 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
     }
     *ran = best != nullptr;
     return best ? best->launch(a, S, kc, W, s) : hipSuccess;
+}
+
+// Rows and tiles of one list launch in 32 bits for every tile of the table; beyond
+// LIST_FLOPS (tens of microseconds alone) a product gains nothing from company and
+// takes its own tile.
+constexpr double LIST_FLOPS = 4e9;
+
+bool list_eligible(const GemmArgs &a, int32_t dtype) {
+    const int64_t es = (int64_t)elem_size(dtype), lim = (int64_t)1 << 31;
+    return a.m >= 1 && a.k >= 1 && a.n >= 16 / es && ((uintptr_t)a.A % 4) == 0 &&
+           ((uintptr_t)a.B % 4) == 0 && a.m < lim && a.k < lim && 128 * a.lda * es < lim &&
+           (64 * a.ldb + 128) * es < lim && a.ldc < lim &&
+           2.0 * (double)a.m * (double)a.n * (double)a.k <= LIST_FLOPS;
+}
+
+// The products (list_eligible, any order) in launches of up to LIST_MAX, longest k
+// first, each launch on the tile with the least estimate: its tiles' shares of the
+// busy compute units, but no less than its longest tile alone.
+hipError_t run_direct_list(const GemmArgs *p, int64_t count, int32_t dtype, int cus, hipStream_t s) {
+    const DirectTile *t = dtype == MGEMM_F32 ? kDirectF32 : kDirectF64;
+    const int cnt = dtype == MGEMM_F32 ? (int)(sizeof kDirectF32 / sizeof kDirectF32[0])
+                                       : (int)(sizeof kDirectF64 / sizeof kDirectF64[0]);
+    if (cus <= 0) cus = 256;
+    for (int64_t i0 = 0; i0 < count; i0 += LIST_MAX) {
+        const int c = (int)std::min<int64_t>(LIST_MAX, count - i0);
+        const DirectTile *best = nullptr;
+        double tb = 0.0;
+        for (int i = 0; i < cnt; ++i) {
+            const DirectTile &d = t[i];
+            const double area = d.bm * d.bn / 4096.0;
+            double sum = 0.0, longest = 0.0;
+            for (int j = 0; j < c; ++j) {
+                const GemmArgs &g = p[i0 + j];
+                const double tiles = (double)((g.m + d.bm - 1) / d.bm) * (double)((g.n + d.bn - 1) / d.bn);
+                const double ks = (double)((g.k + d.bk - 1) / d.bk * d.bk);
+                sum += tiles * (d.each + d.rate * ks * area * (d.alone / d.resident + 1.0));
+                longest = std::max(longest, d.each + d.rate * ks * area * (d.alone + 1.0));
+            }
+            const double ti = d.start + std::max(sum / cus, longest);
+            if (!best || ti < tb) {
+                best = &d;
+                tb = ti;
+            }
+        }
+        const hipError_t he = best->list(p + i0, c, s);
+        if (he != hipSuccess) return he;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------

@@ -245,7 +245,7 @@ bool cfg_registered(int32_t dtype, const mgemm_cfg &c) {
 
 // Whether work enqueued on s is being captured into a graph (then nothing may be
 // launched and waited for on another stream); unknown counts as capturing.
-static bool capturing(hipStream_t s) {
+bool capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
@@ -272,7 +272,7 @@ constexpr int64_t SPLITK_MIN_K = 256;
 constexpr int64_t SPLITK_FIRST_K = 2048;
 constexpr int SPLITK_MAX = 16;
 
-static int compute_units() {
+int compute_units() {
     static int cached[64] = {0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
@@ -509,6 +509,21 @@ int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg,
     return 0;
 }
 
+int32_t run_plan(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s) {
+    if (cp.main_rows > 0) {
+        GemmArgs am = a;
+        am.m = cp.main_rows;
+        hipError_t he = launch_whole(cp, am, dtype, s);
+        if (he != hipSuccess) return hip_error(he, "gemm launch");
+        return run_splitk(cp.e, rows_from(a, cp.main_rows, elem_size(dtype)), dtype, cp.al, cp.sp,
+                          s);
+    }
+    if (cp.sp.S > 1) return run_splitk(cp.e, a, dtype, cp.al, cp.sp, s);
+    hipError_t he = launch_whole(cp, a, dtype, s);
+    if (he != hipSuccess) return hip_error(he, "gemm launch");
+    return 0;
+}
+
 // gemm_ex: argument checks, configuration choice and launch.
 static int32_t gemm_impl(int64_t m, int64_t n, int64_t k, double alpha, const void *A,
                          int64_t lda, const void *B, int64_t ldb, double beta, void *C,
@@ -530,18 +545,7 @@ static int32_t gemm_impl(int64_t m, int64_t n, int64_t k, double alpha, const vo
     CallPlan cp;
     rc = plan_call(a, dtype, cfg, !capturing(s) && !capturing(g_stream), cp);
     if (rc) return rc;
-    if (cp.main_rows > 0) {
-        GemmArgs am = a;
-        am.m = cp.main_rows;
-        hipError_t he = launch_whole(cp, am, dtype, s);
-        if (he != hipSuccess) return hip_error(he, "gemm launch");
-        return run_splitk(cp.e, rows_from(a, cp.main_rows, elem_size(dtype)), dtype, cp.al, cp.sp,
-                          s);
-    }
-    if (cp.sp.S > 1) return run_splitk(cp.e, a, dtype, cp.al, cp.sp, s);
-    hipError_t he = launch_whole(cp, a, dtype, s);
-    if (he != hipSuccess) return hip_error(he, "gemm launch");
-    return 0;
+    return run_plan(cp, a, dtype, s);
 }
 
 }  // namespace mgemm

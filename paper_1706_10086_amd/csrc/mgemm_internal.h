@@ -122,6 +122,11 @@ bool pipe_splitk_eligible(const GemmArgs &a, int32_t dtype);
 hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void *W, int cus,
                       hipStream_t s, bool *ran);
 
+// Whole FP64 or FP32 products that may share a launch, and their launches (no order
+// among them): the built-in choice's bits without a split of k.
+bool list_eligible(const GemmArgs &a, int32_t dtype);
+hipError_t run_direct_list(const GemmArgs *p, int64_t count, int32_t dtype, int cus, hipStream_t s);
+
 // The default batched plan's kernel: 64 x 64 direct-load tiles, work-group b taking
 // entry b / BATCH_LISTS of list b % BATCH_LISTS of the tile map (`longest`: entries of
 // the longest list).
@@ -175,6 +180,12 @@ inline GemmArgs rows_from(const GemmArgs &a, int64_t r, size_t es) {
 // device only when model_may_launch, else only its cached choices count.
 int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg, bool model_may_launch,
                   CallPlan &cp);
+// A planned product on stream s, its k ranges in the library workspace.
+int32_t run_plan(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s);
+// Whether work enqueued on s is being captured into a graph.
+bool capturing(hipStream_t s);
+// Compute units of the current device (0 if unknown).
+int compute_units();
 // A whole product (or its whole rows) of a plan, on stream s.
 hipError_t launch_whole(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s);
 // The S partial products of a split plan into W (at least S*m*n elements) and

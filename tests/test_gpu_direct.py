@@ -120,3 +120,57 @@ def test_default_plan_mixes_direct_and_register_staged(dev, dtype):
         print(f"default plan dtype={mg.DTYPE_NAMES[dtype]} {s}", flush=True)
         assert torch.equal(c, w), s
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [mg.F64, mg.F32])
+def test_lists_share_launches(dev, dtype):
+    """gemm_batched: more products than one launch takes, with empty ones, alpha = 0, a
+    split of k and rows shorter than a load unit among them, give the bits of gemm
+    called in turn; so do lists whose products depend on each other (a result read as
+    A, as B, rewritten, or interleaved with another's rows)."""
+    tdt = torch.float64 if dtype == mg.F64 else torch.float32
+    g = torch.Generator(device=dev)
+    g.manual_seed(23)
+    rng = np.random.RandomState(5)
+    shapes = [tuple(int(2.0 ** rng.uniform(0, 8)) for _ in range(3)) for _ in range(130)]
+    shapes += [(100, 60, 5000), (64, 64, 4096), (700, 650, 600), (33, 2, 9), (40, 1, 40), (1, 1, 1)]
+    As = [embedded(m, k, i % 3, i % 2, tdt, dev, g)[1] for i, (m, n, k) in enumerate(shapes)]
+    Bs = [embedded(k, n, i % 2, i % 4, tdt, dev, g)[1] for i, (m, n, k) in enumerate(shapes)]
+    Cs = [embedded(m, n, i % 5, 0, tdt, dev, g)[1] for i, (m, n, k) in enumerate(shapes)]
+    As.append(torch.zeros((0, 8), device=dev, dtype=tdt))
+    Bs.append(torch.zeros((8, 4), device=dev, dtype=tdt))
+    Cs.append(torch.zeros((0, 4), device=dev, dtype=tdt))
+    alphas = [0.0 if i == 3 else 1.25 for i in range(len(As))]
+    want = [c.clone() for c in Cs]
+    print(f"list of {len(As)} dtype={mg.DTYPE_NAMES[dtype]}", flush=True)
+    mg.set_stream(torch.cuda.current_stream())
+    mg.gemm_batched(As, Bs, Cs, alphas, -0.5)
+    for a, b, c, al in zip(As, Bs, want, alphas):
+        mg.gemm(a, b, c, al, -0.5)
+    torch.cuda.synchronize()
+    for i, (c, w) in enumerate(zip(Cs, want)):
+        assert torch.equal(c, w), (i, tuple(c.shape))
+
+    def chain():
+        x = [torch.rand((48, 48), device=dev, dtype=tdt, generator=g) for _ in range(5)]
+        wide = torch.rand((48, 96), device=dev, dtype=tdt, generator=g)
+        l, r = wide[:, :48], wide[:, 48:]
+        # x[2] is read as A, then as B, then rewritten; the halves of `wide` interleave
+        return x + [wide], [(x[0], x[1], x[2]), (x[2], x[1], x[3]), (x[0], x[2], x[4]),
+                            (x[1], x[0], x[2]), (x[0], x[1], l), (x[1], x[0], r)]
+
+    for lo, hi in ((0, 2), (0, 3), (0, 6), (1, 4), (4, 6)):
+        bufs, probs = chain()
+        probs = probs[lo:hi]
+        saved = [b.clone() for b in bufs]
+        print(f"dependent list {lo}:{hi}", flush=True)
+        mg.gemm_batched(*zip(*probs), 1.0, 0.5)
+        torch.cuda.synchronize()
+        got = [b.clone() for b in bufs]
+        for b, s in zip(bufs, saved):
+            b.copy_(s)
+        for a, b, c in probs:
+            mg.gemm(a, b, c, 1.0, 0.5)
+        torch.cuda.synchronize()
+        for b, w in zip(got, bufs):
+            assert torch.equal(b, w), (lo, hi)
