@@ -191,9 +191,12 @@ struct CrtGemmArgs {
     int accumulate;        // add the previous passes' residues already in R
 };
 
-// 32x32 accumulator element r of lane l: row 8(r/4) + 4(l/32) + r%4, column l%32.
-__device__ inline int crt_acc_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-
+// Bound: the matrix cores and LDS together (98 KB of fragment reads and 32 KB of
+// loads per 1030 cycles of products), at the clock their power leaves.  At 4096^3 the
+// epilogue counted as much as the k-loop while it divided twice per element and stored
+// single bytes: see the figures there.
+// 32x32 accumulator element r of lane l: row (here a column of C) 8(r/4) + 4(l/32) +
+// r%4, column (here a row of C) l%32.
 template <int WGM, int WGN, bool SWZ>
 __global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4)))
 crt_gemm_kernel(CrtGemmArgs a) {
@@ -282,7 +285,7 @@ crt_gemm_kernel(CrtGemmArgs a) {
             for (int mt = 0; mt < FM; ++mt) {
 #pragma unroll
                 for (int nt = 0; nt < FN; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[kk][mt], fb[kk][nt],
+                    acc[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[kk][nt], fa[kk][mt],
                                                                          acc[mt][nt], 0, 0, 0);
                 read_a(nst, kk, mt);
                 constexpr int every = 2 * FM / LOADS > 0 ? 2 * FM / LOADS : 1;
@@ -327,22 +330,49 @@ crt_gemm_kernel(CrtGemmArgs a) {
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));       // no load lands after this point
 
-    uint8_t *R = a.R + t * a.plane_r;
-    const int64_t row0 = (int64_t)tm * CRT_TILE + wm * WTM;
-    const int64_t col0 = (int64_t)tn * CRT_TILE + wn * WTN + (lane & 31);
+    // Residues modulo p, packed and stored through LDS.  The products were formed
+    // transposed (columns of B as the MFMA's rows), so elements 4g..4g+3 of a lane are
+    // four neighbouring columns of one row: one 32-bit word, 32 words per lane, and the
+    // tile's rows leave in whole 256-byte runs.
+    const uint32_t M = (uint32_t)(0x100000000ull / (uint32_t)p);   // uniform
+    const uint32_t bias = (uint32_t)p * (uint32_t)((1 << 30) / p + 1);
+    constexpr int ROWB = CRT_TILE + 8;                 // LDS row stride (bytes)
+    static_assert(CRT_TILE * ROWB <= NST * L::STAGE * 16, "the tile's residues fit the stages");
+    uint8_t *R = a.R + t * a.plane_r + (int64_t)tm * CRT_TILE * a.np + (int64_t)tn * CRT_TILE;
+    uint8_t *tile = (uint8_t *)lds;
+    __syncthreads();                                   // every wave is done with the stages
 #pragma unroll
     for (int mt = 0; mt < FM; ++mt)
 #pragma unroll
         for (int nt = 0; nt < FN; ++nt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                uint8_t *dst = R + (row0 + mt * 32 + crt_acc_row(lane, r)) * a.np + col0 + nt * 32;
-                int v = acc[mt][nt][r] % p;
-                if (a.accumulate) v += *dst;
-                v %= p;
-                if (v < 0) v += p;
-                *dst = (uint8_t)v;
+            for (int g = 0; g < 4; ++g) {
+                const int row = wm * WTM + mt * 32 + (lane & 31);
+                const int col = wn * WTN + nt * 32 + 8 * g + 4 * (lane >> 5);
+                uint32_t old = 0;
+                if (a.accumulate) old = *(const uint32_t *)(R + (int64_t)row * a.np + col);
+                uint32_t word = 0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // |acc| <= 2^30, so u < 2^31 + 256; the quotient estimate is the
+                    // floor of u / p or one less
+                    const uint32_t u = (uint32_t)acc[mt][nt][4 * g + r] + bias;
+                    uint32_t v = u - __umulhi(u, M) * (uint32_t)p;
+                    v = min(v, v - (uint32_t)p);
+                    if (a.accumulate) {
+                        v += (old >> (8 * r)) & 0xFFu;
+                        v = min(v, v - (uint32_t)p);
+                    }
+                    word |= v << (8 * r);
+                }
+                *(uint32_t *)(tile + row * ROWB + col) = word;
             }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < CRT_TILE * CRT_TILE / 8 / NT; ++i) {
+        const int u = i * NT + tid, row = u / (CRT_TILE / 8), c = u % (CRT_TILE / 8) * 8;
+        *(uint64_t *)(R + (int64_t)row * a.np + c) = *(const uint64_t *)(tile + row * ROWB + c);
+    }
 }
 
 // ---------------------------------------------------------------------------
