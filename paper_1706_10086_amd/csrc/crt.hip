@@ -79,18 +79,21 @@ __device__ inline void residues_of(double a, int8_t (&r)[CRT_MODULI]) {
     }
 }
 
-// Thread per (row, 8 consecutive k) of A; rows >= m and k >= k give zeros.
+// Block per 8 rows x 256 k of A, thread per (row, 8 consecutive k): a wave writes runs
+// of 512 bytes (8 rows of one chunk), and neighbouring blocks read on along the rows
+// (blocks of 32 rows x 64 k, one memory channel under all rows of a power-of-two
+// leading dimension, took 184 us at 4096^2 instead of 135).  Rows >= m and k >= k give
+// zeros.
 __global__ void __launch_bounds__(256)
 crt_residue_a_kernel(const double *__restrict__ A, int64_t m, int64_t k, int64_t lda,
                      const int *__restrict__ e, int bits, int8_t *__restrict__ Q, int64_t mp,
                      int64_t kp) {
-    const int64_t groups = kp / 8;
-    const int64_t total = mp * groups;
+    const int tid = threadIdx.x;
+    const int64_t chunk = (int64_t)blockIdx.x * 4 + (tid >> 6);
+    const int64_t p0 = chunk * CRT_KSTEP + (tid & 7) * 8;
+    if (p0 >= kp) return;
     const int64_t plane = mp * kp;
-    for (int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; gid < total;
-         gid += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = gid / groups;
-        const int64_t p0 = (gid - i * groups) * 8;
+    for (int64_t i = (int64_t)blockIdx.y * 8 + ((tid >> 3) & 7); i < mp; i += (int64_t)gridDim.y * 8) {
         const int ex = i < m ? e[i] : 0;
         uint32_t w[CRT_MODULI][2];
 #pragma unroll
@@ -105,9 +108,10 @@ crt_residue_a_kernel(const double *__restrict__ A, int64_t m, int64_t k, int64_t
             for (int t = 0; t < CRT_MODULI; ++t)
                 w[t][v >> 2] |= (uint32_t)(uint8_t)r[t] << (8 * (v & 3));
         }
+        int8_t *dst = Q + (chunk * mp + i) * CRT_KSTEP + (tid & 7) * 8;
 #pragma unroll
         for (int t = 0; t < CRT_MODULI; ++t)
-            *(uint2 *)(Q + t * plane + i * kp + p0) = make_uint2(w[t][0], w[t][1]);
+            *(uint2 *)(dst + t * plane) = make_uint2(w[t][0], w[t][1]);
     }
 }
 
@@ -147,7 +151,7 @@ crt_residue_b_kernel(const double *__restrict__ B, int64_t k, int64_t n, int64_t
     const int64_t plane = np * kp;
 #pragma unroll
     for (int t = 0; t < CRT_MODULI; ++t)
-        *(u32x4 *)(Q + t * plane + j * kp + p0 + pg) = u32x4{w[t][0], w[t][1], w[t][2], w[t][3]};
+        *(u32x4 *)(Q + t * plane + p0 * np + j * CRT_KSTEP + pg) = u32x4{w[t][0], w[t][1], w[t][2], w[t][3]};
 }
 
 // ---------------------------------------------------------------------------
@@ -159,7 +163,10 @@ crt_residue_b_kernel(const double *__restrict__ B, int64_t k, int64_t n, int64_t
 // stages are filled by direct global->LDS loads NST-1 stages ahead, and every
 // fragment register is refilled from the next stage right after its last use.
 // Operands are zero-padded to whole tiles and stages, so no load or store needs
-// a bounds test.
+// a bounds test.  A plane holds its chunks of 64 k one after another, each with the 64
+// bytes of all rows in turn, so a stage's 256 rows are one run of 16 KB: with rows of
+// kp bytes every 128-byte line was asked for twice, half each time (4096^3: 1.43e8 L2
+// requests and 1207 us, 7.3e7 and 1140 us in chunks).
 constexpr int G_KS = CRT_KSTEP;                 // k per stage
 constexpr int G_PASS = (1 << 16) / G_KS;        // stages per launch: |acc| < 2^16 * 2^14
 
@@ -185,7 +192,7 @@ struct CrtGemmArgs {
     const int8_t *QB;
     uint8_t *R;
     int64_t plane_a, plane_b, plane_r;
-    int64_t kp, np;
+    int64_t np;
     int tiles_m, tiles_n;
     int ch0, ch1;          // stages [ch0, ch1) of this pass (at most 2^16 k)
     int accumulate;        // add the previous passes' residues already in R
@@ -224,8 +231,11 @@ crt_gemm_kernel(CrtGemmArgs a) {
     int tm, tn;
     tile_of_block(lid - t * tiles, 0, a.tiles_m, a.tiles_n, tm, tn);
     const int p = kModuliDev[t];
-    const int8_t *qa = a.QA + t * a.plane_a + (int64_t)tm * CRT_TILE * a.kp;
-    const int8_t *qb = a.QB + t * a.plane_b + (int64_t)tn * CRT_TILE * a.kp;
+    const int8_t *qa = a.QA + t * a.plane_a + (int64_t)tm * CRT_TILE * G_KS;
+    const int8_t *qb = a.QB + t * a.plane_b + (int64_t)tn * CRT_TILE * G_KS;
+    // bytes from one chunk of 64 k to the next
+    const int64_t chunk_a = (int64_t)a.tiles_m * CRT_TILE * G_KS,
+                  chunk_b = (int64_t)a.tiles_n * CRT_TILE * G_KS;
 
     // per-lane source offsets: LDS unit u of a stage holds row r, logical unit c
     uint32_t off[LOADS];
@@ -235,12 +245,13 @@ crt_gemm_kernel(CrtGemmArgs a) {
         const int v = u < L::AUNITS ? u : u - L::AUNITS;
         const int r = v / L::ROW, pu = v % L::ROW;
         const int c = SWZ ? (pu ^ L::sw(r)) : (pu < 4 ? pu : 3);
-        off[i] = (uint32_t)r * (uint32_t)a.kp + (uint32_t)c * 16u;
+        off[i] = (uint32_t)r * (uint32_t)G_KS + (uint32_t)c * 16u;
     }
     // load instruction i of chunk `chunk` into stage st
     auto issue_one = [&](int i, int chunk, int st) {
         const int first = i * NT + wave * 64;                     // uniform per wave
-        const int8_t *src = (first < L::AUNITS ? qa : qb) + (int64_t)chunk * G_KS + off[i];
+        const bool in_a = (i + 1) * NT <= L::AUNITS || (i * NT < L::AUNITS && first < L::AUNITS);
+        const int8_t *src = (in_a ? qa + chunk * chunk_a : qb + chunk * chunk_b) + off[i];
         __builtin_amdgcn_global_load_lds((const void *)src,
                                          (__attribute__((address_space(3))) void *)(lds + st * L::STAGE + first),
                                          16, 0, 0);
@@ -302,8 +313,8 @@ crt_gemm_kernel(CrtGemmArgs a) {
 
     // stages of this pass, counted from its first.  Chunks 0..NST-2 in flight;
     // wait for chunk 0 (the loads of NST-2 chunks may remain)
-    qa += (int64_t)a.ch0 * G_KS;
-    qb += (int64_t)a.ch0 * G_KS;
+    qa += (int64_t)a.ch0 * chunk_a;
+    qb += (int64_t)a.ch0 * chunk_b;
     const int nst = a.ch1 - a.ch0;
 #pragma unroll
     for (int c = 0; c < NST - 1; ++c) issue(c < nst ? c : nst - 1, c);
@@ -524,11 +535,9 @@ hipError_t crt_launch(const GemmArgs &g, hipStream_t s, const int *e, const int 
                       int8_t *QA, int8_t *QB, uint8_t *R, int64_t mp, int64_t np, int64_t kp) {
     const CrtTables &tb = tables();
     {
-        const int64_t groups = mp * (kp / 8);
-        int64_t blocks = (groups + 255) / 256;
-        if (blocks > 1 << 20) blocks = 1 << 20;
-        hipLaunchKernelGGL(crt_residue_a_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                           (const double *)g.A, g.m, g.k, g.lda, e, bits, QA, mp, kp);
+        const unsigned gy = (unsigned)(mp / 8 < 65535 ? mp / 8 : 65535);
+        hipLaunchKernelGGL(crt_residue_a_kernel, dim3((unsigned)((kp + 255) / 256), gy), dim3(256), 0,
+                           s, (const double *)g.A, g.m, g.k, g.lda, e, bits, QA, mp, kp);
         hipLaunchKernelGGL(crt_residue_b_kernel, dim3((unsigned)(np / 64), (unsigned)(kp / 64)),
                            dim3(256), 0, s, (const double *)g.B, g.k, g.n, g.ldb, fexp, bits, QB,
                            np, kp);
@@ -541,7 +550,6 @@ hipError_t crt_launch(const GemmArgs &g, hipStream_t s, const int *e, const int 
         ga.plane_a = mp * kp;
         ga.plane_b = np * kp;
         ga.plane_r = mp * np;
-        ga.kp = kp;
         ga.np = np;
         ga.tiles_m = (int)(mp / CRT_TILE);
         ga.tiles_n = (int)(np / CRT_TILE);
