@@ -24,6 +24,7 @@
 // same operand width), this needs 16 products of the full width, each a plain
 // int8 GEMM.
 #include <limits.h>
+#include <math.h>
 
 #include "mgemm_internal.h"
 
@@ -54,29 +55,61 @@ __constant__ int kModuliDev[CRT_MODULI] = {modulus(0),  modulus(1),  modulus(2),
 // ---------------------------------------------------------------------------
 // 2. Residues.
 // ---------------------------------------------------------------------------
-// Residues of the integer a (|a| < 2^62, held exactly in a double) modulo each p,
-// as int8 in [-p/2, p/2).  a = hi 2^32 + lo with 0 <= lo < 2^32, |hi| < 2^30, and in
-// 16-bit digits a = h1 2^48 + h0 2^32 + l1 2^16 + l0 (h1 signed, |h1| < 2^14), so
-// a = h1 c48 + h0 c32 + l1 c16 + l0 (mod p) with c_e = 2^e mod p < 2^8: a sum below
-// 2^26 in magnitude of 24-bit products; a multiple of p above 2^22 makes it
-// non-negative for one unsigned reduction.
-__device__ inline void residues_of(double a, int8_t (&r)[CRT_MODULI]) {
+// Residues of integers a (|a| < 2^62, held exactly in doubles) modulo each p, as int8
+// in [-p/2, p/2).  a + 2^63 is a 64-bit word of eight bytes y_i, so a = sum_i y_i c_i +
+// K (mod p) with c_i = 2^(8i) mod p and K = -2^63 mod p: two byte dot products with K
+// as their start.  The sum s stays below 2^19.3, and with h = p / 2 rounded down the
+// quotient floor((s + h) / p) is the high word of 16 (s + h) times ceil(2^28 / p), both
+// factors below 2^24 (exact for every s + h < 2^20: the factor's excess adds less than
+// 2^-8 < 1 / p).  Five instructions per residue, where 16-bit digits with 32-bit
+// products and a 32-bit reduction took about twelve.
+__host__ __device__ constexpr uint32_t byte_consts(int t, int e0) {
+    return (uint32_t)pow2_mod(t, e0) | (uint32_t)pow2_mod(t, e0 + 8) << 8 |
+           (uint32_t)pow2_mod(t, e0 + 16) << 16 | (uint32_t)pow2_mod(t, e0 + 24) << 24;
+}
+
+// The bytes of a + 2^63 as two words (lo, hi).
+struct Bytes8 {
+    uint32_t lo, hi;
+};
+
+__device__ inline Bytes8 bytes_of(double a) {
     const double hi = floor(a * 0x1p-32);
-    const double lo = a - hi * 0x1p32;
-    const int hi_i = (int)hi;
-    const uint32_t lo_u = (uint32_t)lo;
-    const int h1 = hi_i >> 16, h0 = hi_i & 0xFFFF;
-    const int l1 = (int)(lo_u >> 16), l0 = (int)(lo_u & 0xFFFFu);
+    return {(uint32_t)(a - hi * 0x1p32), (uint32_t)(int)hi ^ 0x80000000u};
+}
+
+// Residue t of the integer with bytes y, in the low byte.
+template <int t>
+__device__ inline uint32_t residue(Bytes8 y) {
+    constexpr int p = modulus(t), h = p / 2;
+    constexpr uint32_t K = (uint32_t)((p - pow2_mod(t, 63)) % p);
+    constexpr uint32_t M = ((1u << 28) + p - 1) / p;
+    static_assert(M < (1u << 24) && 8 * 255 * 255 + 2 * 256 < (1 << 20), "24-bit quotient");
+    const uint32_t s = __builtin_amdgcn_udot4(
+        y.hi, byte_consts(t, 32), __builtin_amdgcn_udot4(y.lo, byte_consts(t, 0), K, false), false);
+    const uint32_t u = (s << 4) + 16u * (uint32_t)h;
+    const uint32_t q = (uint32_t)(((uint64_t)(u & 0xFFFFFFu) * M) >> 32);
+    return s - (uint32_t)__mul24((int)q, p);
+}
+
+// The low bytes of four words as one word.
+__device__ inline uint32_t pack4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
+    const uint32_t cd = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
+    return ab | cd << 16;
+}
+
+// Residues t.. of N integers (N a multiple of 4), N / 4 words per modulus, each handed
+// to store(modulus, words).
+template <int N, int t = 0, typename F>
+__device__ inline void residues_each(const Bytes8 (&y)[N], F store) {
+    uint32_t w[N / 4];
 #pragma unroll
-    for (int t = 0; t < CRT_MODULI; ++t) {
-        const int p = modulus(t);
-        const int bias = p * ((1 << 22) / p + 1);              // > 2^22, multiple of p
-        const int sum = __mul24(h1, pow2_mod(t, 48)) + __mul24(h0, pow2_mod(t, 32)) +
-                        __mul24(l1, pow2_mod(t, 16)) + l0 + bias;
-        int v = (int)((uint32_t)sum % (uint32_t)p);               // [0, p)
-        if (v > (p - 1) / 2) v -= p;                              // [-p/2, p/2)
-        r[t] = (int8_t)v;
-    }
+    for (int i = 0; i < N / 4; ++i)
+        w[i] = pack4(residue<t>(y[4 * i]), residue<t>(y[4 * i + 1]), residue<t>(y[4 * i + 2]),
+                     residue<t>(y[4 * i + 3]));
+    store(t, w);
+    if constexpr (t + 1 < CRT_MODULI) residues_each<N, t + 1>(y, store);
 }
 
 // Block per 8 rows x 256 k of A, thread per (row, 8 consecutive k): a wave writes runs
@@ -95,23 +128,16 @@ crt_residue_a_kernel(const double *__restrict__ A, int64_t m, int64_t k, int64_t
     const int64_t plane = mp * kp;
     for (int64_t i = (int64_t)blockIdx.y * 8 + ((tid >> 3) & 7); i < mp; i += (int64_t)gridDim.y * 8) {
         const int ex = i < m ? e[i] : 0;
-        uint32_t w[CRT_MODULI][2];
-#pragma unroll
-        for (int t = 0; t < CRT_MODULI; ++t) w[t][0] = w[t][1] = 0;
+        Bytes8 y[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
             const int64_t p = p0 + v;
-            const double x = (i < m && p < k) ? trunc(ldexp(A[i * lda + p], bits - ex)) : 0.0;
-            int8_t r[CRT_MODULI];
-            residues_of(x, r);
-#pragma unroll
-            for (int t = 0; t < CRT_MODULI; ++t)
-                w[t][v >> 2] |= (uint32_t)(uint8_t)r[t] << (8 * (v & 3));
+            y[v] = bytes_of((i < m && p < k) ? trunc(ldexp(A[i * lda + p], bits - ex)) : 0.0);
         }
         int8_t *dst = Q + (chunk * mp + i) * CRT_KSTEP + (tid & 7) * 8;
-#pragma unroll
-        for (int t = 0; t < CRT_MODULI; ++t)
-            *(uint2 *)(dst + t * plane) = make_uint2(w[t][0], w[t][1]);
+        residues_each(y, [&](int t, const uint32_t (&w)[2]) {
+            *(uint2 *)(dst + t * plane) = make_uint2(w[0], w[1]);
+        });
     }
 }
 
@@ -136,22 +162,14 @@ crt_residue_b_kernel(const double *__restrict__ B, int64_t k, int64_t n, int64_t
     const int64_t j = j0 + jc;
     const int fe = j < n ? fexp[j] : INT_MIN;
     const int ex = fe == INT_MIN ? 0 : fe;
-    uint32_t w[CRT_MODULI][4];
+    Bytes8 y[16];
 #pragma unroll
-    for (int t = 0; t < CRT_MODULI; ++t) w[t][0] = w[t][1] = w[t][2] = w[t][3] = 0;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const double x = trunc(ldexp(tile[pg + v][jc], bits - ex));
-        int8_t r[CRT_MODULI];
-        residues_of(x, r);
-#pragma unroll
-        for (int t = 0; t < CRT_MODULI; ++t)
-            w[t][v >> 2] |= (uint32_t)(uint8_t)r[t] << (8 * (v & 3));
-    }
+    for (int v = 0; v < 16; ++v) y[v] = bytes_of(trunc(ldexp(tile[pg + v][jc], bits - ex)));
     const int64_t plane = np * kp;
-#pragma unroll
-    for (int t = 0; t < CRT_MODULI; ++t)
-        *(u32x4 *)(Q + t * plane + p0 * np + j * CRT_KSTEP + pg) = u32x4{w[t][0], w[t][1], w[t][2], w[t][3]};
+    int8_t *dst = Q + p0 * np + j * CRT_KSTEP + pg;
+    residues_each(y, [&](int t, const uint32_t (&w)[4]) {
+        *(u32x4 *)(dst + t * plane) = u32x4{w[0], w[1], w[2], w[3]};
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -391,12 +409,12 @@ crt_gemm_kernel(CrtGemmArgs a) {
 // ---------------------------------------------------------------------------
 // With P the moduli's product, M_t = P / p_t and W_t = M_t (M_t^-1 mod p_t) < P,
 // S = sum_t r_t W_t is congruent to C' modulo P; q = round(S / P) is found from
-// sum_t r_t (W_t / P) in FP64 (|C'| <= P/4 keeps S/P within 1/4 of q, far above
+// the upper digits of S in FP64 (|C'| <= P/4 keeps S/P within 1/4 of q, far above
 // the estimate's error), and C' = S - q P is computed modulo 2^128, which is exact
 // because |C'| < 2^127.
 struct CrtReconArgs {
-    uint32_t w[CRT_MODULI][4];      // W_t as four 32-bit limbs, least significant first
-    double wf[CRT_MODULI];          // W_t / P
+    uint32_t w[CRT_MODULI / 4][16]; // byte j of W_4g..W_4g+3, four to a word
+    double digit[4];                // 2^(64 + 16 i) / P
     uint32_t pl[4];                 // P as four 32-bit limbs
 };
 
@@ -422,31 +440,51 @@ __device__ inline double i128_to_double(uint64_t hi, uint64_t lo) {
     return neg ? -v : v;
 }
 
-// C' of one element from its 16 residues r_t (byte v of each word rr[t]).
-__device__ inline double crt_value(const uint64_t (&rr)[CRT_MODULI], int v, const CrtReconArgs &rc) {
-    // S = sum_t r_t W_t by 32-bit limbs: each limb sum < 16 * 255 * 2^32 < 2^44
-    // (measured faster than 20-bit limbs with 24-bit multiplies)
-    uint64_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-    double qf = 0.0;
+// C' of one element from its 16 residues, four to a word (r[g] holds t = 4g..4g+3).
+// Byte j of the moduli's weights forms sum_t r_t W_t[j] < 2^20 by four byte dot
+// products; pairs of bytes make digits of 16 bits (below 2^29), whose upper four give
+// S / P (the lower four are below 2^-45 of P), and pairs of digits 32-bit limbs.
+__device__ inline double crt_value(const uint32_t (&r)[CRT_MODULI / 4], const CrtReconArgs &rc) {
+    uint32_t d[8];
 #pragma unroll
-    for (int t = 0; t < CRT_MODULI; ++t) {
-        const uint32_t r = (uint32_t)(rr[t] >> (8 * v)) & 0xFFu;
-        s0 += (uint64_t)r * rc.w[t][0];
-        s1 += (uint64_t)r * rc.w[t][1];
-        s2 += (uint64_t)r * rc.w[t][2];
-        s3 += (uint64_t)r * rc.w[t][3];
-        qf = fma((double)r, rc.wf[t], qf);
+    for (int i = 0; i < 8; ++i) {
+        uint32_t s0 = 0, s1 = 0;
+#pragma unroll
+        for (int g = 0; g < CRT_MODULI / 4; ++g) {
+            s0 = __builtin_amdgcn_udot4(r[g], rc.w[g][2 * i], s0, false);
+            s1 = __builtin_amdgcn_udot4(r[g], rc.w[g][2 * i + 1], s1, false);
+        }
+        d[i] = s0 + (s1 << 8);
     }
+    double qf = (double)d[4] * rc.digit[0];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) qf = fma((double)d[4 + i], rc.digit[i], qf);
     const uint32_t q = (uint32_t)rint(qf);         // < 16 * 256
-    // subtract q P limb by limb (q P_l < 2^44); carries propagate as signed values,
-    // everything modulo 2^128
-    int64_t d0 = (int64_t)s0 - (int64_t)((uint64_t)q * rc.pl[0]);
-    int64_t d1 = (int64_t)s1 - (int64_t)((uint64_t)q * rc.pl[1]) + (d0 >> 32);
-    int64_t d2 = (int64_t)s2 - (int64_t)((uint64_t)q * rc.pl[2]) + (d1 >> 32);
-    int64_t d3 = (int64_t)s3 - (int64_t)((uint64_t)q * rc.pl[3]) + (d2 >> 32);
+    // limbs below 2^46, minus q P limb by limb (q P_l < 2^44); carries propagate as
+    // signed values, everything modulo 2^128
+    auto limb = [&](int l) {
+        return (int64_t)((uint64_t)d[2 * l] + ((uint64_t)d[2 * l + 1] << 16)) -
+               (int64_t)((uint64_t)q * rc.pl[l]);
+    };
+    const int64_t d0 = limb(0);
+    const int64_t d1 = limb(1) + (d0 >> 32);
+    const int64_t d2 = limb(2) + (d1 >> 32);
+    const int64_t d3 = limb(3) + (d2 >> 32);
     const uint64_t lo = ((uint64_t)(uint32_t)d1 << 32) | (uint32_t)d0;
     const uint64_t hi = ((uint64_t)(uint32_t)d3 << 32) | (uint32_t)d2;
     return i128_to_double(hi, lo);
+}
+
+// Bytes 0..3 of four words a_t, as four words of one byte of each.
+__device__ inline void transpose4(const uint32_t (&a)[4], uint32_t (&c)[4]) {
+    const uint32_t l01 = __builtin_amdgcn_perm(a[1], a[0], 0x05010400u);
+    const uint32_t h01 = __builtin_amdgcn_perm(a[1], a[0], 0x07030602u);
+    const uint32_t l23 = __builtin_amdgcn_perm(a[3], a[2], 0x05010400u);
+    const uint32_t h23 = __builtin_amdgcn_perm(a[3], a[2], 0x07030602u);
+    c[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
+    c[1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
+    c[2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
+    c[3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
 }
 
 // Thread per 8 consecutive elements of a row of C: one 8-byte load per modulus.
@@ -460,16 +498,31 @@ crt_reconstruct_kernel(const uint8_t *__restrict__ R, int64_t plane_r, int64_t n
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
          idx += (int64_t)gridDim.x * blockDim.x) {
         const int64_t i = idx / n8, j0 = (idx - i * n8) * 8;
-        uint64_t rr[CRT_MODULI];
+        // residues of element v: rr[v][g] holds t = 4g..4g+3
+        uint32_t rr[8][CRT_MODULI / 4];
 #pragma unroll
-        for (int t = 0; t < CRT_MODULI; ++t)
-            rr[t] = *(const uint64_t *)(R + t * plane_r + i * np + j0);
+        for (int g = 0; g < CRT_MODULI / 4; ++g) {
+            uint32_t lo[4], hi[4], cl[4], ch[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const uint2 w = *(const uint2 *)(R + (4 * g + x) * plane_r + i * np + j0);
+                lo[x] = w.x;
+                hi[x] = w.y;
+            }
+            transpose4(lo, cl);
+            transpose4(hi, ch);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                rr[x][g] = cl[x];
+                rr[4 + x][g] = ch[x];
+            }
+        }
         const int ei = e[i];
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
             const int64_t j = j0 + v;
             if (j >= n) break;
-            const double cv = crt_value(rr, v, rc);
+            const double cv = crt_value(rr[v], rc);
             const int fe = fexp[j];
             const double val = ldexp(cv, ei + (fe == INT_MIN ? 0 : fe) - two_bits);
             double *c = C + i * ldc + j;
@@ -506,9 +559,13 @@ struct CrtTables {
             }
             const long long inv = ((s0 % p) + p) % p;       // r0 == 1: coprime moduli
             const u128 W = M * (u128)inv;                    // < P: inv < p
-            for (int l = 0; l < 4; ++l) rc.w[t][l] = (uint32_t)(W >> (32 * l));
-            rc.wf[t] = (double)W / (double)P;
+            for (int j = 0; j < 16; ++j) {
+                uint32_t &w = rc.w[t / 4][j];
+                if (t % 4 == 0) w = 0;
+                w |= (uint32_t)(uint8_t)(W >> (8 * j)) << (8 * (t % 4));
+            }
         }
+        for (int i = 0; i < 4; ++i) rc.digit[i] = ldexp(1.0, 64 + 16 * i) / (double)P;
         for (int l = 0; l < 4; ++l) rc.pl[l] = (uint32_t)(P >> (32 * l));
     }
 };
