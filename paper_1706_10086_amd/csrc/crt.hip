@@ -588,9 +588,8 @@ int crt_operand_bits(int64_t k) {
     return b;
 }
 
-hipError_t crt_launch(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
-                      int8_t *QA, int8_t *QB, uint8_t *R, int64_t mp, int64_t np, int64_t kp) {
-    const CrtTables &tb = tables();
+hipError_t crt_residues(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
+                        int8_t *QA, int8_t *QB, int64_t mp, int64_t np, int64_t kp) {
     {
         const unsigned gy = (unsigned)(mp / 8 < 65535 ? mp / 8 : 65535);
         hipLaunchKernelGGL(crt_residue_a_kernel, dim3((unsigned)((kp + 255) / 256), gy), dim3(256), 0,
@@ -599,6 +598,13 @@ hipError_t crt_launch(const GemmArgs &g, hipStream_t s, const int *e, const int 
                            dim3(256), 0, s, (const double *)g.B, g.k, g.n, g.ldb, fexp, bits, QB,
                            np, kp);
     }
+    return hipGetLastError();
+}
+
+hipError_t crt_products(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
+                        const int8_t *QA, const int8_t *QB, uint8_t *R, int64_t mp, int64_t np,
+                        int64_t kp) {
+    const CrtTables &tb = tables();
     {
         CrtGemmArgs ga;
         ga.QA = QA;

@@ -100,8 +100,8 @@ __device__ inline void tile_of_block(int bid, int nblocks, int tiles_m, int tile
 }
 
 // Modular-integer (Ozaki scheme II) emulation: operands are padded to whole
-// CRT_TILE x CRT_KSTEP blocks; crt_launch runs the residue, product and
-// reconstruction kernels on exponents already computed (e per row of A, fexp per
+// CRT_TILE x CRT_KSTEP blocks; crt_residues and then crt_products (products and
+// reconstruction) run on exponents already computed (e per row of A, fexp per
 // column of B, INT_MIN for an all-zero column).  Workspace: QA and QB hold
 // CRT_MODULI int8 planes of mp x kp and np x kp, R CRT_MODULI byte planes of
 // mp x np.
@@ -109,8 +109,11 @@ constexpr int CRT_MODULI = 16;
 constexpr int CRT_TILE = 256;
 constexpr int CRT_KSTEP = 64;
 int crt_operand_bits(int64_t k);
-hipError_t crt_launch(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
-                      int8_t *QA, int8_t *QB, uint8_t *R, int64_t mp, int64_t np, int64_t kp);
+hipError_t crt_residues(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
+                        int8_t *QA, int8_t *QB, int64_t mp, int64_t np, int64_t kp);
+hipError_t crt_products(const GemmArgs &g, hipStream_t s, const int *e, const int *fexp, int bits,
+                        const int8_t *QA, const int8_t *QB, uint8_t *R, int64_t mp, int64_t np,
+                        int64_t kp);
 
 // Whether the plan may cut k on 128 x 128 tiles (rows of whole 16-byte loads).
 bool pipe_splitk_eligible(const GemmArgs &a, int32_t dtype);

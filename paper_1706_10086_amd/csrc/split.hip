@@ -25,8 +25,8 @@
 //          FP8 e4m3 slices, b1 = 4, b = 5 bits, round to nearest, S = 11 (66 pairs);
 //          int8 slices, b1 = b = 7 bits, round toward zero, S = 8 (36 pairs).
 //
-// Workspace (device, owned by the library, grown on demand): exponents, a
-// non-finite flag and the slices, laid out per row as [row][k-chunk][slice][KC]
+// Workspace (device, owned by the library, grown on demand): exponents
+// and the slices, laid out per row as [row][k-chunk][slice][KC]
 // so that one k-chunk of all slices of a row is one contiguous run.
 #include <limits.h>
 
@@ -99,12 +99,18 @@ constexpr int PBN = 128;     // pair kernel tile columns
 // ---------------------------------------------------------------------------
 // 1. Scale.
 // ---------------------------------------------------------------------------
-__global__ void split_init_kernel(int *fexp, int64_t np, int *flag) {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < np;
-         j += (int64_t)gridDim.x * blockDim.x)
-        fexp[j] = INT_MIN;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
-}
+// Largest |x| of a run of elements and whether one is NaN or Inf, without a branch per
+// element: the magnitude by FP64 maxima (which skip NaN), finiteness by the largest
+// upper word.
+struct MaxAbs {
+    double mx = 0.0;
+    uint32_t top = 0;
+    __device__ inline void take(double v) {
+        mx = fmax(mx, fabs(v));
+        top = max(top, (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7FFFFFFFu);
+    }
+    __device__ inline bool bad() const { return top >= 0x7FF00000u; }
+};
 
 __device__ inline int exponent_of(double mx) {
     int ex = 0;
@@ -112,22 +118,24 @@ __device__ inline int exponent_of(double mx) {
     return ex;
 }
 
-// One 256-thread block per row (grid-stride over rows).
+// One 256-thread block per row of A (grid-stride over rows); also clears the column
+// exponents for the kernel after it.  *flag (host memory) becomes 1 where an element is
+// not finite.
 __global__ void __launch_bounds__(256)
 split_row_scale_kernel(const double *__restrict__ A, int64_t m, int64_t k, int64_t lda,
-                       int *__restrict__ e, int *flag) {
+                       int *__restrict__ e, int *__restrict__ fexp, int64_t np, int *flag) {
     __shared__ double red[4];
     __shared__ int bad_any[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int64_t j = (int64_t)blockIdx.x * 256 + tid; j < np; j += (int64_t)gridDim.x * 256)
+        fexp[j] = INT_MIN;
     for (int64_t i = blockIdx.x; i < m; i += gridDim.x) {
-        double mx = 0.0;
-        int bad = 0;
+        MaxAbs x;
         const double *row = A + i * lda;
-        for (int64_t p = tid; p < k; p += 256) {
-            double v = row[p];
-            if (!isfinite(v)) bad = 1;
-            else mx = fmax(mx, fabs(v));
-        }
+#pragma unroll 4
+        for (int64_t p = tid; p < k; p += 256) x.take(row[p]);
+        double mx = x.mx;
+        int bad = x.bad();
         for (int off = 32; off > 0; off >>= 1) {
             mx = fmax(mx, __shfl_xor(mx, off));
             bad |= __shfl_xor(bad, off);
@@ -143,10 +151,11 @@ split_row_scale_kernel(const double *__restrict__ A, int64_t m, int64_t k, int64
     }
 }
 
-// Thread per column, 64 rows per block row; exponents merged with atomicMax
-// (the exponent is non-decreasing in |x|).  Untouched (all-zero) columns keep
-// INT_MIN and are read as exponent 0.
-constexpr int COL_ROWS = 64;
+// Thread per column, 32 rows per block row, eight loads in flight; exponents merged
+// with atomicMax (the exponent is non-decreasing in |x|).  Untouched (all-zero) columns
+// keep INT_MIN and are read as exponent 0.  (64 rows with a branch per element took 22
+// us at 2048^2 and 45 us at 4096^2.)
+constexpr int COL_ROWS = 32;
 
 __global__ void __launch_bounds__(256)
 split_col_scale_kernel(const double *__restrict__ B, int64_t k, int64_t n, int64_t ldb,
@@ -156,16 +165,16 @@ split_col_scale_kernel(const double *__restrict__ B, int64_t k, int64_t n, int64
     const int64_t nyb = (k + COL_ROWS - 1) / COL_ROWS;
     for (int64_t yb = blockIdx.y; yb < nyb; yb += gridDim.y) {
         const int64_t p0 = yb * COL_ROWS;
-        const int64_t p1 = p0 + COL_ROWS < k ? p0 + COL_ROWS : k;
-        double mx = 0.0;
-        int bad = 0;
-        for (int64_t p = p0; p < p1; ++p) {
-            double v = B[p * ldb + j];
-            if (!isfinite(v)) bad = 1;
-            else mx = fmax(mx, fabs(v));
+        const double *col = B + p0 * ldb + j;
+        MaxAbs x;
+        if (p0 + COL_ROWS <= k) {
+#pragma unroll 8
+            for (int p = 0; p < COL_ROWS; ++p) x.take(col[p * ldb]);
+        } else {
+            for (int64_t p = p0; p < k; ++p, col += ldb) x.take(*col);
         }
-        if (bad) *flag = 1;
-        if (mx > 0.0) atomicMax(fexp + j, exponent_of(mx));
+        if (x.bad()) *flag = 1;
+        if (x.mx > 0.0) atomicMax(fexp + j, exponent_of(x.mx));
     }
 }
 
@@ -861,7 +870,8 @@ struct Workspace {
     std::mutex mtx;
     uint8_t *base = nullptr;
     size_t bytes = 0;
-    int *host_flag = nullptr;        // pinned
+    int *host_flag = nullptr;        // pinned: the scale kernels set it
+    hipEvent_t scaled = nullptr;     // the scale kernels of the current call
     hipEvent_t done = nullptr;       // last split work that used the workspace
 };
 
@@ -879,6 +889,10 @@ static int32_t ws_mark(Workspace &w, hipStream_t s) {
 static int32_t ws_reserve(Workspace &w, size_t bytes) {
     if (!w.done) {
         if (hipEventCreateWithFlags(&w.done, hipEventDisableTiming) != hipSuccess)
+            return set_error(MGEMM_ERR_HIP, "split: event create failed");
+    }
+    if (!w.scaled) {
+        if (hipEventCreateWithFlags(&w.scaled, hipEventDisableTiming) != hipSuccess)
             return set_error(MGEMM_ERR_HIP, "split: event create failed");
     }
     if (!w.host_flag) {
@@ -904,6 +918,37 @@ static int32_t ws_reserve(Workspace &w, size_t bytes) {
     return 0;
 }
 
+// The row and column exponents of g's operands on s, into e and fexp (np entries);
+// scale_check then waits for them (and not for what was queued after them) and reports
+// non-finite input.
+static int32_t scale_launch(const GemmArgs &g, hipStream_t s, Workspace &w, int *e, int *fexp,
+                            int64_t np) {
+    int *flag = nullptr;
+    hipError_t he = hipStreamWaitEvent(s, w.done, 0);
+    if (he == hipSuccess) he = hipHostGetDevicePointer((void **)&flag, w.host_flag, 0);
+    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split: %s", hipGetErrorString(he));
+    *(volatile int *)w.host_flag = 0;      // the previous call has read it
+    hipLaunchKernelGGL(split_row_scale_kernel, dim3((unsigned)(g.m < 65536 ? g.m : 65536)),
+                       dim3(256), 0, s, (const double *)g.A, g.m, g.k, g.lda, e, fexp, np, flag);
+    int64_t gy = (g.k + COL_ROWS - 1) / COL_ROWS;
+    if (gy > 65535) gy = 65535;
+    hipLaunchKernelGGL(split_col_scale_kernel, dim3((unsigned)((g.n + 255) / 256), (unsigned)gy),
+                       dim3(256), 0, s, (const double *)g.B, g.k, g.n, g.ldb, fexp, flag);
+    he = hipGetLastError();
+    if (he == hipSuccess) he = hipEventRecord(w.scaled, s);
+    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split scale: %s", hipGetErrorString(he));
+    return 0;
+}
+
+static int32_t scale_check(Workspace &w, hipStream_t s) {
+    const hipError_t he = hipEventSynchronize(w.scaled);
+    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split scale: %s", hipGetErrorString(he));
+    if (!*(volatile int *)w.host_flag) return 0;
+    // the slicing queued meanwhile only writes the workspace
+    const int32_t rc = ws_mark(w, s);
+    return rc ? rc : set_error(MGEMM_ERR_NONFINITE, "split: A or B holds NaN or Inf");
+}
+
 static inline int64_t round_up(int64_t x, int64_t q) { return (x + q - 1) / q * q; }
 
 // A slice-pair kernel and its launch shape.
@@ -927,33 +972,17 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
     const size_t e_bytes = round_up(mp * 4, 256), f_bytes = round_up(np * 4, 256);
     // the FP8 pair kernel keeps its exact sums (16 bytes per element of C) here
     const size_t s_bytes = pk.sums ? (size_t)mp * np * 16 : 0;
-    const size_t total = e_bytes + f_bytes + 256 + a_bytes + b_bytes + s_bytes;
+    const size_t total = e_bytes + f_bytes + a_bytes + b_bytes + s_bytes;
     int32_t rc = ws_reserve(w, total);
     if (rc) return rc;
     int *e = (int *)w.base;
     int *fexp = (int *)(w.base + e_bytes);
-    int *flag = (int *)(w.base + e_bytes + f_bytes);
-    uint8_t *QA = w.base + e_bytes + f_bytes + 256;
+    uint8_t *QA = w.base + e_bytes + f_bytes;
     uint8_t *QB = QA + a_bytes;
     double *sums = pk.sums ? (double *)(QB + b_bytes) : nullptr;
 
-    hipError_t he = hipStreamWaitEvent(s, w.done, 0);
-    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split: %s", hipGetErrorString(he));
-    hipLaunchKernelGGL(split_init_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s,
-                       fexp, np, flag);
-    hipLaunchKernelGGL(split_row_scale_kernel, dim3((unsigned)(g.m < 65536 ? g.m : 65536)),
-                       dim3(256), 0, s, (const double *)g.A, g.m, g.k, g.lda, e, flag);
-    {
-        int64_t gy = (g.k + COL_ROWS - 1) / COL_ROWS;
-        if (gy > 65535) gy = 65535;
-        hipLaunchKernelGGL(split_col_scale_kernel, dim3((unsigned)((g.n + 255) / 256), (unsigned)gy),
-                           dim3(256), 0, s, (const double *)g.B, g.k, g.n, g.ldb, fexp, flag);
-    }
-    he = hipMemcpyAsync(w.host_flag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (he == hipSuccess) he = hipStreamSynchronize(s);
-    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split scale: %s", hipGetErrorString(he));
-    if (*w.host_flag) return set_error(MGEMM_ERR_NONFINITE, "split: A or B holds NaN or Inf");
-
+    rc = scale_launch(g, s, w, e, fexp, np);
+    if (rc) return rc;
     {
         int64_t groups = mp * (kp / 8);
         int64_t blocks = (groups + 255) / 256;
@@ -964,6 +993,8 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
                            dim3(256), 0, s, (const double *)g.B, g.k, g.n, g.ldb,
                            (const int *)fexp, QB, kp);
     }
+    rc = scale_check(w, s);
+    if (rc) return rc;
 
     PairArgs pa;
     pa.QA = QA;
@@ -989,7 +1020,7 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
         pa.beta = c0 == 0 ? g.beta : 1.0;
         hipLaunchKernelGGL(pk.fn, dim3((unsigned)blocks), dim3(pk.threads), 0, s, pa);
     }
-    he = hipGetLastError();
+    const hipError_t he = hipGetLastError();
     if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split launch: %s", hipGetErrorString(he));
     return ws_mark(w, s);
 }
@@ -1005,33 +1036,22 @@ static int32_t run_crt(const GemmArgs &g, hipStream_t s, Workspace &w) {
     const size_t qa_bytes = (size_t)CRT_MODULI * mp * kp, qb_bytes = (size_t)CRT_MODULI * np * kp;
     const size_t r_bytes = (size_t)CRT_MODULI * mp * np;
     const size_t e_bytes = round_up(mp * 4, 256), f_bytes = round_up(np * 4, 256);
-    int32_t rc = ws_reserve(w, e_bytes + f_bytes + 256 + qa_bytes + qb_bytes + r_bytes);
+    int32_t rc = ws_reserve(w, e_bytes + f_bytes + qa_bytes + qb_bytes + r_bytes);
     if (rc) return rc;
     int *e = (int *)w.base;
     int *fexp = (int *)(w.base + e_bytes);
-    int *flag = (int *)(w.base + e_bytes + f_bytes);
-    int8_t *QA = (int8_t *)(w.base + e_bytes + f_bytes + 256);
+    int8_t *QA = (int8_t *)(w.base + e_bytes + f_bytes);
     int8_t *QB = QA + qa_bytes;
     uint8_t *R = (uint8_t *)(QB + qb_bytes);
 
-    hipError_t he = hipStreamWaitEvent(s, w.done, 0);
-    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "crt: %s", hipGetErrorString(he));
-    hipLaunchKernelGGL(split_init_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s,
-                       fexp, np, flag);
-    hipLaunchKernelGGL(split_row_scale_kernel, dim3((unsigned)(g.m < 65536 ? g.m : 65536)),
-                       dim3(256), 0, s, (const double *)g.A, g.m, g.k, g.lda, e, flag);
-    {
-        int64_t gy = (g.k + COL_ROWS - 1) / COL_ROWS;
-        if (gy > 65535) gy = 65535;
-        hipLaunchKernelGGL(split_col_scale_kernel, dim3((unsigned)((g.n + 255) / 256), (unsigned)gy),
-                           dim3(256), 0, s, (const double *)g.B, g.k, g.n, g.ldb, fexp, flag);
-    }
-    he = hipMemcpyAsync(w.host_flag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (he == hipSuccess) he = hipStreamSynchronize(s);
-    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "crt scale: %s", hipGetErrorString(he));
-    if (*w.host_flag) return set_error(MGEMM_ERR_NONFINITE, "crt: A or B holds NaN or Inf");
-
-    he = crt_launch(g, s, e, fexp, crt_operand_bits(g.k), QA, QB, R, mp, np, kp);
+    rc = scale_launch(g, s, w, e, fexp, np);
+    if (rc) return rc;
+    const int bits = crt_operand_bits(g.k);
+    hipError_t he = crt_residues(g, s, e, fexp, bits, QA, QB, mp, np, kp);
+    if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "crt launch: %s", hipGetErrorString(he));
+    rc = scale_check(w, s);
+    if (rc) return rc;
+    he = crt_products(g, s, e, fexp, bits, QA, QB, R, mp, np, kp);
     if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "crt launch: %s", hipGetErrorString(he));
     return ws_mark(w, s);
 }
