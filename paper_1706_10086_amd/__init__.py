@@ -226,6 +226,11 @@ def configs(dtype: int, need: int = 0) -> list[Cfg]:
 def _stream_handle(stream):
     if stream is None:
         import torch
+        # the handle alone: torch.cuda.current_stream() builds a Stream object around
+        # it, 2.7 us of a call whose product takes 5.5
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -233,11 +238,12 @@ def _stream_handle(stream):
 
 
 def _ld(t) -> int:
-    if t.dim() != 2:
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2:
         raise ValueError("2-D tensor expected")
-    if t.shape[1] > 1 and t.stride(1) != 1:
+    if shape[1] > 1 and stride[1] != 1:
         raise ValueError("unit column stride required")
-    return max(t.stride(0), 1) if t.shape[0] > 1 else max(t.shape[1], 1)
+    return max(stride[0], 1) if shape[0] > 1 else max(shape[1], 1)
 
 
 def dtype_of(t) -> int:
@@ -255,14 +261,19 @@ def _check_operands(dtype: int, *ts) -> None:
     on the current GPU."""
     import torch
     want = torch.float32 if dtype == F32 else torch.float64
-    dev = torch.cuda.current_device() if torch.cuda.is_available() else None
+    Tensor = torch.Tensor
     for t in ts:
-        if not isinstance(t, torch.Tensor):
+        if not isinstance(t, Tensor):
             raise TypeError("torch tensors expected")
-        if t.dtype != want:
+        if t.dtype is not want:
             raise ValueError(f"{DTYPE_NAMES.get(dtype, dtype)} takes {want} tensors, got {t.dtype}")
+    dev = None
     for t in ts:
-        if not t.is_cuda or t.device.index != dev:
+        if not t.is_cuda:
+            raise ValueError("tensors must live on the current GPU")
+        if dev is None:
+            dev = torch.cuda.current_device()
+        if t.get_device() != dev:
             raise ValueError("tensors must live on the current GPU")
 
 
@@ -312,28 +323,30 @@ class _BatchArrays:
     """Host arrays (kept alive) describing a list of problems."""
 
     def __init__(self, As, Bs, Cs, alphas, betas):
-        import numpy as np
         cnt = len(As)
         self.count = cnt
-        self.m = np.array([a.shape[0] for a in As], dtype=np.int64)
-        self.k = np.array([a.shape[1] for a in As], dtype=np.int64)
-        self.n = np.array([b.shape[1] for b in Bs], dtype=np.int64)
-        self.lda = np.array([_ld(a) for a in As], dtype=np.int64)
-        self.ldb = np.array([_ld(b) for b in Bs], dtype=np.int64)
-        self.ldc = np.array([_ld(c) for c in Cs], dtype=np.int64)
+        if len(Bs) != cnt or len(Cs) != cnt:
+            raise ValueError("as many A, B and C expected")
+        # one row per problem, one pass over the tensors: a list of small products
+        # costs more in marshalling than on the GPU
+        rows = []
+        for a, b, c in zip(As, Bs, Cs):
+            lda, ldb, ldc = _ld(a), _ld(b), _ld(c)
+            m, k = a.shape
+            k2, n = b.shape
+            if k2 != k or c.shape != (m, n):
+                raise ValueError("shape mismatch in batch")
+            rows.append((m, n, k, lda, ldb, ldc, a.data_ptr(), b.data_ptr(), c.data_ptr()))
+        # a column each for m n k lda ldb ldc A B C
+        self.cols = np.ascontiguousarray(np.array(rows, dtype=np.int64).reshape(cnt, 9).T)
         self.alpha = np.ascontiguousarray(np.broadcast_to(np.asarray(alphas, dtype=np.float64), (cnt,)))
         self.beta = np.ascontiguousarray(np.broadcast_to(np.asarray(betas, dtype=np.float64), (cnt,)))
-        self.A = (ctypes.c_void_p * cnt)(*[a.data_ptr() for a in As])
-        self.B = (ctypes.c_void_p * cnt)(*[b.data_ptr() for b in Bs])
-        self.C = (ctypes.c_void_p * cnt)(*[c.data_ptr() for c in Cs])
-        for a, b, c in zip(As, Bs, Cs):
-            if a.shape[1] != b.shape[0] or tuple(c.shape) != (a.shape[0], b.shape[1]):
-                raise ValueError("shape mismatch in batch")
 
     def args(self):
-        P = lambda x: x.ctypes.data if hasattr(x, "ctypes") else ctypes.cast(x, ctypes.c_void_p).value
-        return (self.count, P(self.m), P(self.n), P(self.k), P(self.alpha), P(self.A), P(self.lda),
-                P(self.B), P(self.ldb), P(self.beta), P(self.C), P(self.ldc))
+        base, step = self.cols.ctypes.data, 8 * self.count
+        m, n, k, lda, ldb, ldc, A, B, C = (base + i * step for i in range(9))
+        return (self.count, m, n, k, self.alpha.ctypes.data, A, lda, B, ldb,
+                self.beta.ctypes.data, C, ldc)
 
 
 def gemm_batched(As, Bs, Cs, alphas=1.0, betas=0.0, dtype=None) -> None:
