@@ -86,7 +86,16 @@ splitk_reduce_kernel(const T *__restrict__ W, int S, int64_t m, int64_t n, T alp
              col += (int64_t)gridDim.x * 256) {
             const int64_t i = row * n + col;
             T acc = W[i];
-            for (int y = 1; y < S; ++y) acc += W[y * plane + i];
+            // seven planes' loads in flight, added in plane order
+            int y = 1;
+            for (; y + 6 < S; y += 7) {
+                T w[7];
+#pragma unroll
+                for (int j = 0; j < 7; ++j) w[j] = W[(y + j) * plane + i];
+#pragma unroll
+                for (int j = 0; j < 7; ++j) acc += w[j];
+            }
+            for (; y < S; ++y) acc += W[y * plane + i];
             T *c = C + row * ldc + col;
             *c = read_c ? scale_add(alpha, acc, beta, *c) : alpha * acc;
         }

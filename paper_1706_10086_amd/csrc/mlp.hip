@@ -354,16 +354,22 @@ static int step_blocks(const Mlp *p, int64_t rows) {
     return (int)std::min<int64_t>((rows + step_rows(p) - 1) / step_rows(p), cus);
 }
 
+// Elements of one block's gradient share.
+static int64_t share_elems(const Mlp *p) {
+    return (p->P + UPDATE_SHARE - 1) / UPDATE_SHARE * UPDATE_SHARE;
+}
+
 // Loss and gradient of one step on the step kernel, and with lr > 0 Adam's update.
 static void step_launch(Mlp *p, hipStream_t s, float lr, float b1, float b2, float eps) {
-    const MlpStepArgs a{p->I, p->H, p->O, p->B, p->X, p->T, p->M, p->par, p->planes, p->part,
+    const int64_t plane = share_elems(p);
+    const MlpStepArgs a{p->I, p->H, p->O, p->B, p->X, p->T, p->M, p->par, p->planes, plane, p->part,
                         lr > 0.0f ? p->step : (int *)nullptr};
     if (step_rows(p) == 64)
         hipLaunchKernelGGL((mlp_step_kernel<64, 64>), dim3(p->blocks), dim3(512), 0, s, a);
     else
         hipLaunchKernelGGL((mlp_step_kernel<128, 32>), dim3(p->blocks), dim3(512), 0, s, a);
-    hipLaunchKernelGGL(mlp_update_kernel, dim3((unsigned)((p->P + 31) / 32)), dim3(256), 0, s,
-                       p->planes, p->blocks, p->P, p->part, p->loss, p->grad, p->par, p->m, p->v,
+    hipLaunchKernelGGL(mlp_update_kernel, dim3((unsigned)((p->P + 31) / 32)),
+                       dim3(32 * UPDATE_Z), 0, s, p->planes, plane, p->blocks, p->P, p->part, p->loss, p->grad, p->par, p->m, p->v,
                        lr, b1, b2, eps, (const int *)p->step);
 }
 
@@ -577,7 +583,7 @@ int32_t mlp_set_data(void *handle, int64_t rows, const float *X, const float *T,
         {&p->h2, whole ? B * p->H : 0}, {&p->y, whole ? B * p->O : 0},
         {&p->d, whole ? B * p->O : 0}, {&p->dz2, whole ? B * p->H : 0},
         {&p->dz1, whole ? B * p->H : 0},
-        {&p->planes, whole ? planes_elems(p, B) : blocks * p->P},
+        {&p->planes, whole ? planes_elems(p, B) : blocks * share_elems(p)},
         {&p->part, whole ? 2 * tiles3 : 2 * (int64_t)blocks}};
     for (auto &b : bufs) {
         if (b.n == 0) continue;

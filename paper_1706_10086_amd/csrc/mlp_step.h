@@ -19,6 +19,7 @@ struct MlpStepArgs {
     const float *X, *T, *M;       // B x I, B x O, B x O
     const float *par;             // W1 b1 W2 b2 W3 b3
     float *planes;                // one gradient share per block, in parameter order
+    int64_t plane;                // elements from one share to the next
     float *part;                  // 2 floats per block: sum of M, sum of M (y - t)^2
     int *step;                    // Adam step counter, advanced here (may be NULL)
 };
@@ -91,7 +92,7 @@ __device__ __forceinline__ void step_grad(const float *dZ, int zs, const float *
 // Bound: the matrix cores (about 8 products of ROWS x HP x 64 per 64 outputs, two
 // waves per SIMD) and the latency between the barriers.  13600 rows x (6 -> 64 -> 64
 // -> 247): 12 kernels with activations in memory took 231 us a step; this one takes
-// 41 us (about 15 of them the products' matrix-core time) and the update 8.6.
+// 41 us (about 15 of them the products' matrix-core time) and the update 5.8.
 template <int HP, int ROWS>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 mlp_step_kernel(MlpStepArgs a) {
@@ -105,8 +106,7 @@ mlp_step_kernel(MlpStepArgs a) {
     const int I = a.I, H = a.H, O = a.O;
     const float *W1 = a.par, *b1 = W1 + (int64_t)H * I, *W2 = b1 + H, *b2 = W2 + (int64_t)H * H,
                 *W3 = b2 + H, *b3 = W3 + (int64_t)O * H;
-    const int64_t P = (int64_t)H * I + H + (int64_t)H * H + H + (int64_t)O * H + O;
-    float *gW1 = a.planes + blockIdx.x * P, *gb1 = gW1 + (int64_t)H * I, *gW2 = gb1 + H,
+    float *gW1 = a.planes + blockIdx.x * a.plane, *gb1 = gW1 + (int64_t)H * I, *gW2 = gb1 + H,
           *gb2 = gW2 + (int64_t)H * H, *gW3 = gb2 + H, *gb3 = gW3 + (int64_t)O * H;
     if (a.step && blockIdx.x == 0 && tid == 0) *a.step += 1;   // read by the update kernel
 
@@ -278,39 +278,46 @@ mlp_step_kernel(MlpStepArgs a) {
 }
 
 // g = 2 / sum M * (sum of the nb gradient shares, in a fixed order) for 32 parameters
-// per block, eight threads to a parameter, and with lr > 0 Adam's update of them (step
+// per block, 16 threads to a parameter, and with lr > 0 Adam's update of them (step
 // number *step); block 0 also writes the loss sum M (y - t)^2 / sum M.
 //
-// Bound: the shares' bytes (nb x P x 4, 18 MB at 213 blocks x 20.6 k parameters).
-__global__ void __launch_bounds__(256)
-mlp_update_kernel(const float *__restrict__ planes, int nb, int64_t P,
+// Bound: the shares' bytes (nb x P x 4, 18 MB at 213 blocks x 20.6 k parameters) and the
+// latency of two rounds of loads.  Eight threads to a parameter with one load in flight
+// took 11.5 us, with eight 8.6; 16 threads, eight loads and shares on 256-byte
+// boundaries 5.8.
+constexpr int UPDATE_Z = 16, UPDATE_SHARE = 64;      // shares in multiples of this many elements
+
+__global__ void __launch_bounds__(32 * UPDATE_Z)
+mlp_update_kernel(const float *__restrict__ planes, int64_t plane, int nb, int64_t P,
                   const float *__restrict__ part, float *__restrict__ loss, float *__restrict__ grad,
                   float *__restrict__ p, float *__restrict__ m, float *__restrict__ v, float lr,
                   float b1, float b2, float eps, const int *step) {
-    __shared__ float s_cnt[256], s_sq[256], s_g[256];
+    __shared__ float s_cnt[256], s_sq[256], s_g[32 * UPDATE_Z];
     const int tid = threadIdx.x;
     const int64_t i = (int64_t)blockIdx.x * 32 + (tid & 31);
     float g = 0.0f;
-    if (i < P) {
-        // eight loads in flight (their sum in plane order)
-        int z = tid >> 5;
-        for (; z + 56 < nb; z += 64) {
+    if (i < P)
+        for (int z = tid >> 5; z < nb; z += 8 * UPDATE_Z) {
             float w[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) w[j] = planes[(int64_t)(z + 8 * j) * P + i];
+            for (int j = 0; j < 8; ++j) {
+                const int zj = z + UPDATE_Z * j;
+                w[j] = planes[(int64_t)(zj < nb ? zj : z) * plane + i];
+                if (zj >= nb) w[j] = 0.0f;
+            }
 #pragma unroll
             for (int j = 0; j < 8; ++j) g += w[j];
         }
-        for (; z < nb; z += 8) g += planes[(int64_t)z * P + i];
-    }
     s_g[tid] = g;
-    float cnt = 0.0f, sq = 0.0f;
-    for (int z = tid; z < nb; z += 256) {
-        cnt += part[2 * z];
-        sq += part[2 * z + 1];
+    if (tid < 256) {
+        float cnt = 0.0f, sq = 0.0f;
+        for (int z = tid; z < nb; z += 256) {
+            cnt += part[2 * z];
+            sq += part[2 * z + 1];
+        }
+        s_cnt[tid] = cnt;
+        s_sq[tid] = sq;
     }
-    s_cnt[tid] = cnt;
-    s_sq[tid] = sq;
     __syncthreads();
     for (int h = 128; h > 0; h >>= 1) {
         if (tid < h) {
@@ -322,7 +329,7 @@ mlp_update_kernel(const float *__restrict__ planes, int nb, int64_t P,
     const float total = s_cnt[0] > 0.0f ? s_cnt[0] : 1.0f;
     if (blockIdx.x == 0 && tid == 0) *loss = s_sq[0] / total;
     if (tid >= 32 || i >= P) return;
-    for (int z = 1; z < 8; ++z) g += s_g[tid + 32 * z];
+    for (int z = 1; z < UPDATE_Z; ++z) g += s_g[tid + 32 * z];
     g *= 2.0f / total;
     grad[i] = g;
     if (!(lr > 0.0f)) return;
