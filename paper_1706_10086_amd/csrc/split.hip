@@ -29,6 +29,7 @@
 // and the slices, laid out per row as [row][k-chunk][slice][KC]
 // so that one k-chunk of all slices of a row is one contiguous run.
 #include <limits.h>
+#include <math.h>
 
 #include <mutex>
 
@@ -91,6 +92,9 @@ struct FmtE4M3 {
 
 // bytes of one (row, k-chunk) run: all S slices of KC elements
 template <typename F> constexpr int run_bytes() { return F::S * F::KC * F::ELEM; }
+
+// exponents of the units of the two exact sums
+constexpr int BF16_HI = -34, BF16_LO = -61, E4M3_HI = -28, E4M3_LO = -58, I8_HI = -35, I8_LO = -63;
 
 constexpr int KPAD = 64;     // k padded to a multiple of 64 (slice-B transpose tile)
 constexpr int PBM = 64;      // pair kernel tile rows
@@ -294,7 +298,41 @@ struct PairArgs {
     double alpha, beta;
     int tiles_m, tiles_n;
     double *sums;       // FP8 pair kernel: exact level sums, 32 per lane (else unused)
+    // Tail launch (PART kernels): work-group (x, y) takes the y-th range of `range`
+    // chunks of tile tile0 + x and leaves its exact sums hi and lo in `part`
+    // (split_combine_kernel adds the ranges) instead of storing C.
+    int tile0;
+    int64_t range;
+    double *part;
 };
+
+// The tile and the chunk range of this work-group.  A tail's tiles follow the whole
+// ones in the order those take within an XCD.  The values are uniform but computed on
+// vector registers: without readfirstlane the FP8 kernel spills 21 registers more and
+// reloads them between its direct loads (each reload waits for those in flight: a
+// 64-k chunk takes 9.3 us instead of 4.4).
+template <bool PART>
+__device__ __attribute__((always_inline)) inline void pair_work(const PairArgs &a, int &tm, int &tn,
+                                                                int64_t &c0, int64_t &c1) {
+    if (PART) {
+        tile_of_block(a.tile0 + (int)blockIdx.x, a.tile0 ? 0 : (int)gridDim.x, a.tiles_m, a.tiles_n,
+                      tm, tn);
+        tm = __builtin_amdgcn_readfirstlane(tm);
+        tn = __builtin_amdgcn_readfirstlane(tn);
+        const int b0 = __builtin_amdgcn_readfirstlane((int)a.ch0 + (int)blockIdx.y * (int)a.range);
+        const int b1 = b0 + (int)a.range;
+        c0 = b0;
+        c1 = __builtin_amdgcn_readfirstlane(b1 < (int)a.ch1 ? b1 : (int)a.ch1);
+    } else {
+        tile_of_block(blockIdx.x, gridDim.x, a.tiles_m, a.tiles_n, tm, tn);
+        c0 = a.ch0;
+        c1 = a.ch1;
+    }
+}
+
+__host__ __device__ constexpr double exp2i(int e) {
+    return e < 0 ? 0.5 * exp2i(e + 1) : e > 0 ? 2.0 * exp2i(e - 1) : 1.0;
+}
 
 // 32x32 MFMA accumulator element r of lane l -> (row, column) in the wave block
 __device__ inline int acc_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
@@ -312,6 +350,53 @@ __device__ inline void store_c(const PairArgs &a, int64_t row, int64_t col, doub
 #pragma clang fp contract(off)
         *c = a.alpha * val + a.beta * *c;
     }
+}
+
+// One element's exact sums: combined, rounded once and stored, or left for
+// split_combine_kernel.  (r, c): its place in the TM x TN tile.
+template <bool PART, int TM, int TN, int HI, int LO>
+__device__ __attribute__((always_inline)) inline void finish(const PairArgs &a, int64_t m0, int64_t n0,
+                                                             int r, int c, double hi, double lo) {
+    if (PART) {
+        double *p = a.part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (2 * TM * TN) + r * TN + c;
+        p[0] = hi;
+        p[TM * TN] = lo;
+    } else {
+        constexpr double unit_hi = exp2i(HI), unit_lo = exp2i(LO);
+        store_c(a, m0 + r, n0 + c, fma(hi, unit_hi, lo * unit_lo));
+    }
+}
+
+// The ranges' sums of one tail tile (blockIdx.x) added -- exact integers in any order --
+// then combined and rounded once, as the whole-tile kernels do.  Bound by the sums' bytes.
+// LANES: the FP8 kernel's running sums (its four waves' 64 lanes x 16 hi, 16 lo), which
+// hold the range's sums as they are; else two TM x TN planes.
+template <int TM, int TN, int HI, int LO, bool LANES>
+__global__ void __launch_bounds__(256)
+split_combine_kernel(PairArgs a, int ranges) {
+    int tm, tn;
+    int64_t c0, c1;
+    pair_work<true>(a, tm, tn, c0, c1);
+    constexpr int AREA = TM * TN;
+    constexpr double unit_hi = exp2i(HI), unit_lo = exp2i(LO);
+    const int e = (int)blockIdx.y * 256 + (int)threadIdx.x;
+    int r = e / TN, c = e % TN, at = e, lo_at = AREA;
+    if (LANES) {
+        const int lane = e & 63, v = (e >> 6) & 15, wave = e >> 10;
+        r = (wave >> 1) * 32 + acc_row(lane, v);
+        c = (wave & 1) * 32 + (lane & 31);
+        at = wave * 2048 + v * 64 + lane;
+        lo_at = 1024;
+    }
+    const double *p = (LANES ? a.sums : a.part) + (int64_t)blockIdx.x * 2 * AREA + at;
+    const int64_t step = (int64_t)gridDim.x * 2 * AREA;
+    double hi = 0.0, lo = 0.0;
+#pragma unroll 4
+    for (int y = 0; y < ranges; ++y) {
+        hi += p[y * step];
+        lo += p[y * step + lo_at];
+    }
+    store_c(a, (int64_t)tm * TM + r, (int64_t)tn * TN + c, fma(hi, unit_hi, lo * unit_lo));
 }
 
 template <typename F>
@@ -487,6 +572,7 @@ __device__ __attribute__((always_inline)) inline void q_issue_loads(
     for (int i = 0; i < Q_LOADS; ++i) q_issue_one(a, i, a_row0, b_row0, ch, stage, wave, lane);
 }
 
+template <bool PART>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 split_pairs_i8_pipe_kernel(PairArgs a) {
     __shared__ u32x4 lds[3 * Q_STAGE];
@@ -495,7 +581,8 @@ split_pairs_i8_pipe_kernel(PairArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     int tm, tn;
-    tile_of_block(blockIdx.x, gridDim.x, a.tiles_m, a.tiles_n, tm, tn);
+    int64_t range0, range1;
+    pair_work<PART>(a, tm, tn, range0, range1);
     const int64_t m0 = (int64_t)tm * Q_BM, n0 = (int64_t)tn * Q_BN;
     const int r32 = lane & 31, kh = lane >> 5;
     const int a_off0 = (wm * 64 + r32) * Q_SROW + kh;            // m-tile 0
@@ -539,7 +626,7 @@ split_pairs_i8_pipe_kernel(PairArgs a) {
         }
     };
 
-    const uint32_t c0 = (uint32_t)a.ch0, c1 = (uint32_t)a.ch1;
+    const uint32_t c0 = (uint32_t)range0, c1 = (uint32_t)range1;
     q_issue_loads(a, ar0, br0, c0, lds, wave, lane);
     q_issue_loads(a, ar0, br0, c0 + 1 < c1 ? c0 + 1 : c0, lds + Q_STAGE, wave, lane);
     __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
@@ -575,8 +662,8 @@ split_pairs_i8_pipe_kernel(PairArgs a) {
             lo = lo + (double)acc[5][mt][r] * 0x1p14;
             lo = lo + (double)acc[6][mt][r] * 0x1p7;
             lo = lo + (double)acc[7][mt][r];
-            const double v = fma(hi, 0x1p-35, lo * 0x1p-63);
-            store_c(a, m0 + wm * 64 + mt * 32 + acc_row(lane, r), n0 + wn * 32 + r32, v);
+            finish<PART, Q_BM, Q_BN, I8_HI, I8_LO>(
+                a, m0, n0, wm * 64 + mt * 32 + acc_row(lane, r), wn * 32 + r32, hi, lo);
         }
 }
 
@@ -600,6 +687,7 @@ constexpr int R_BLOCK = 16;                              // chunks per flush cyc
 static_assert(R_AUNITS % 64 == 0 && R_STAGE % 64 == 0, "a wave's loads lie in one operand");
 static_assert(R_NST * R_STAGE * 16 <= 163840, "LDS");
 
+template <bool PART>
 __global__ void __launch_bounds__(R_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 split_pairs_bf16_pipe_kernel(PairArgs a) {
     __shared__ u32x4 lds[R_NST * R_STAGE];
@@ -608,7 +696,8 @@ split_pairs_bf16_pipe_kernel(PairArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     int tm, tn;
-    tile_of_block(blockIdx.x, gridDim.x, a.tiles_m, a.tiles_n, tm, tn);
+    int64_t range0, range1;
+    pair_work<PART>(a, tm, tn, range0, range1);
     const int64_t m0 = (int64_t)tm * R_BM, n0 = (int64_t)tn * R_BN;
     const int r32 = lane & 31, kh = lane >> 5;
     const int a_off = (wm * 32 + r32) * R_SROW + kh;
@@ -679,8 +768,8 @@ split_pairs_bf16_pipe_kernel(PairArgs a) {
         acc[lv] = v16f{};
     };
 
-    const uint32_t c0 = (uint32_t)a.ch0;
-    const int nch = (int)(a.ch1 - a.ch0);         // a multiple of R_BLOCK
+    const uint32_t c0 = (uint32_t)range0;
+    const int nch = (int)(range1 - range0);       // a multiple of R_BLOCK
     const uint32_t clast = c0 + (uint32_t)nch - 1;
 #pragma unroll
     for (int c = 0; c < R_NST - 1; ++c) {
@@ -726,10 +815,9 @@ split_pairs_bf16_pipe_kernel(PairArgs a) {
 
     // exact value = hi 2^-34 + lo 2^-61, rounded once
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const double v = fma(hi[r], 0x1p-34, lo[r] * 0x1p-61);
-        store_c(a, m0 + wm * 32 + acc_row(lane, r), n0 + wn * 32 + r32, v);
-    }
+    for (int r = 0; r < 16; ++r)
+        finish<PART, R_BM, R_BN, BF16_HI, BF16_LO>(a, m0, n0, wm * 32 + acc_row(lane, r), wn * 32 + r32,
+                                             hi[r], lo[r]);
 }
 
 // FP8 e4m3: 4 waves (2 x 2, one per SIMD) own a 64 x 64 tile of C, each wave a
@@ -759,6 +847,7 @@ static_assert((2 * E_AUNITS + E_BUNITS) * 16 <= 163840, "LDS");
 
 typedef int v8i_t __attribute__((ext_vector_type(8)));
 
+template <bool PART>
 __global__ void __launch_bounds__(E_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 split_pairs_e4m3_kernel(PairArgs a) {
     __shared__ u32x4 lds[2 * E_AUNITS + E_BUNITS];      // A stage 0, A stage 1, B stage
@@ -767,7 +856,8 @@ split_pairs_e4m3_kernel(PairArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     int tm, tn;
-    tile_of_block(blockIdx.x, gridDim.x, a.tiles_m, a.tiles_n, tm, tn);
+    int64_t range0, range1;
+    pair_work<PART>(a, tm, tn, range0, range1);
     const int64_t m0 = (int64_t)tm * E_BM, n0 = (int64_t)tn * E_BN;
     const int r32 = lane & 31, kh = lane >> 5;
     // fragment of slice s: 32 bytes (units 4s + 2kh, +1) of the wave's row / column
@@ -804,7 +894,8 @@ split_pairs_e4m3_kernel(PairArgs a) {
     for (int l = 0; l < 11; ++l) acc[l] = v16f{};
     // this lane's exact sums in the workspace: hi r at sums[r * 64], lo r at
     // sums[(16 + r) * 64] (lanes adjacent, so each access is one coalesced run)
-    double *sums = a.sums + ((int64_t)blockIdx.x * 4 + wave) * 32 * 64 + lane;
+    double *sums = a.sums +
+                   (((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave) * 32 * 64 + lane;
 #pragma unroll
     for (int r = 0; r < 32; ++r) sums[r * 64] = 0.0;
 
@@ -827,7 +918,7 @@ split_pairs_e4m3_kernel(PairArgs a) {
         for (int lv = 0; lv < 11; ++lv) acc[lv] = v16f{};
     };
 
-    const uint32_t c0 = (uint32_t)a.ch0, c1 = (uint32_t)a.ch1;
+    const uint32_t c0 = (uint32_t)range0, c1 = (uint32_t)range1;
     issue(c0, 0);
     for (uint32_t c = c0; c < c1; ++c) {
         const int ast = (int)((c - c0) & 1);
@@ -853,12 +944,13 @@ split_pairs_e4m3_kernel(PairArgs a) {
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
+    if (PART) return;                                     // the sums are the range's result
     // exact value = hi 2^-28 + lo 2^-58, rounded once
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const double v = fma(sums[r * 64], 0x1p-28, sums[(16 + r) * 64] * 0x1p-58);
-        store_c(a, m0 + wm * 32 + acc_row(lane, r), n0 + wn * 32 + r32, v);
-    }
+    for (int r = 0; r < 16; ++r)
+        finish<false, E_BM, E_BN, E4M3_HI, E4M3_LO>(a, m0, n0, wm * 32 + acc_row(lane, r),
+                                                    wn * 32 + r32, sums[r * 64],
+                                                    sums[(16 + r) * 64]);
 }
 
 // ---------------------------------------------------------------------------
@@ -958,7 +1050,59 @@ struct PairKernel {
     int kpad;         // k padded to a multiple of this (a multiple of KPAD)
     int chunk_mult;   // each pass covers a multiple of this many chunks
     bool sums = false;  // needs PairArgs::sums (16 bytes per element of C)
+    double chunk_us = 0.0;            // a work-group's time per chunk (0: no split tail)
+    void (*part_fn)(PairArgs) = nullptr;
+    void (*combine_fn)(PairArgs, int) = nullptr;
 };
+
+// How one pass runs: tiles [0, whole) whole, the others with the pass's chunks cut into
+// `ranges` ranges of `range` chunks.
+struct PairPlan {
+    int64_t whole;
+    int ranges;
+    int64_t range;
+};
+
+// A split tail where it pays.  A work-group has a compute unit to itself, so T tiles
+// take ceil(T / CUs) rounds, and the last round may hold a few tiles -- or a small
+// product's only round.  The sums are exact integers, so a tile's chunks may be cut
+// between work-groups and the ranges added in any order with the same bits.  Estimate:
+// rounds times (chunks x chunk_us + PAIR_FIXED_US), and for the tail the combining
+// launch and its bytes; the cut must win 3 %.  Pair products and combination, whole and
+// with the cut: FP8 166x467x2087 (32 tiles, 7 ranges) 144 and 41 us, 1475x138x2052
+// (96 tiles, 2 ranges) 148 and 87, 2384x142x2890 (152 tiles, 3 ranges) 207 and 164.  No
+// cut where the tail nearly fills its round (int8 1500x2301x3107: 176 tiles on 256 units).
+constexpr double PAIR_FIXED_US = 6.0, COMBINE_US = 5.0, COMBINE_BYTES_PER_US = 4e6;
+constexpr int PAIR_RANGES_MAX = 32;
+
+static PairPlan pair_plan(int64_t tiles, int64_t chunks, const PairKernel &pk, int cus) {
+    PairPlan best{tiles, 1, chunks};
+    if (!(pk.chunk_us > 0.0) || cus <= 0) return best;
+    auto rounds = [&](int64_t wgs) { return (double)((wgs + cus - 1) / cus); };
+    const double whole_us = (double)chunks * pk.chunk_us + PAIR_FIXED_US;
+    double t_best = 0.97 * rounds(tiles) * whole_us;
+    const int64_t t1 = tiles / cus * cus, t2 = tiles - t1;
+    if (t2 == 0) return best;
+    int64_t last = 0;
+    for (int want = 2; want <= PAIR_RANGES_MAX; ++want) {
+        const int64_t r = ((chunks + want - 1) / want + pk.chunk_mult - 1) / pk.chunk_mult *
+                          pk.chunk_mult;
+        if (r >= chunks) break;
+        if (r == last) continue;
+        last = r;
+        const int64_t n = (chunks + r - 1) / r;
+        if (t2 * n > 4 * (int64_t)cus) break;
+        const double bytes = (double)(t2 * pk.tile_m * pk.tile_n) * 16.0 * 2.0 * (double)n;
+        const double t = rounds(t1) * whole_us +
+                         rounds(t2 * n) * ((double)r * pk.chunk_us + PAIR_FIXED_US) + COMBINE_US +
+                         bytes / COMBINE_BYTES_PER_US;
+        if (t < t_best) {
+            t_best = t;
+            best = PairPlan{t1, (int)n, r};
+        }
+    }
+    return best;
+}
 
 constexpr int64_t SPLIT_PAD = 128;   // m and n padded to a multiple of every pair tile
 
@@ -972,14 +1116,35 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
     const size_t e_bytes = round_up(mp * 4, 256), f_bytes = round_up(np * 4, 256);
     // the FP8 pair kernel keeps its exact sums (16 bytes per element of C) here
     const size_t s_bytes = pk.sums ? (size_t)mp * np * 16 : 0;
+    const int64_t blocks = (mp / pk.tile_m) * (np / pk.tile_n);
+    const int64_t pass_ch = max_pass_k / F::KC;
+    // chunks holding data, rounded up to the kernel's multiple (zero slices)
+    const int64_t kch = round_up((g.k + F::KC - 1) / F::KC, pk.chunk_mult);
+    // every pass but the last covers pass_ch chunks
+    const int cus = compute_units();
+    PairPlan plans[2] = {pair_plan(blocks, pass_ch < kch ? pass_ch : kch, pk, cus),
+                         pair_plan(blocks, kch - (kch - 1) / pass_ch * pass_ch, pk, cus)};
+    size_t part_bytes = 0;   // one tail's (hi, lo) per element and range
+    for (const PairPlan &pl : plans)
+        if (pl.ranges > 1) {
+            const size_t bytes = (size_t)(blocks - pl.whole) * pl.ranges * pk.tile_m * pk.tile_n * 16;
+            part_bytes = bytes > part_bytes ? bytes : part_bytes;
+        }
     const size_t total = e_bytes + f_bytes + a_bytes + b_bytes + s_bytes;
-    int32_t rc = ws_reserve(w, total);
+    int32_t rc = ws_reserve(w, total + part_bytes);
+    if (rc == MGEMM_ERR_NOMEM && part_bytes) {
+        // no room for the ranges' sums: every tile whole
+        plans[0] = plans[1] = PairPlan{blocks, 1, kch};
+        part_bytes = 0;
+        rc = ws_reserve(w, total);
+    }
     if (rc) return rc;
     int *e = (int *)w.base;
     int *fexp = (int *)(w.base + e_bytes);
     uint8_t *QA = w.base + e_bytes + f_bytes;
     uint8_t *QB = QA + a_bytes;
     double *sums = pk.sums ? (double *)(QB + b_bytes) : nullptr;
+    double *part = part_bytes ? (double *)(QB + b_bytes + s_bytes) : nullptr;
 
     rc = scale_launch(g, s, w, e, fexp, np);
     if (rc) return rc;
@@ -1010,15 +1175,24 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
     pa.tiles_m = (int)(mp / pk.tile_m);
     pa.tiles_n = (int)(np / pk.tile_n);
     pa.sums = sums;
-    const int64_t blocks = (int64_t)pa.tiles_m * pa.tiles_n;
-    const int64_t pass_ch = max_pass_k / F::KC;
-    // chunks holding data, rounded up to the kernel's multiple (zero slices)
-    const int64_t kch = round_up((g.k + F::KC - 1) / F::KC, pk.chunk_mult);
     for (int64_t c0 = 0; c0 < kch; c0 += pass_ch) {
+        const PairPlan &pl = plans[c0 + pass_ch < kch ? 0 : 1];
         pa.ch0 = c0;
         pa.ch1 = c0 + pass_ch < kch ? c0 + pass_ch : kch;
         pa.beta = c0 == 0 ? g.beta : 1.0;
-        hipLaunchKernelGGL(pk.fn, dim3((unsigned)blocks), dim3(pk.threads), 0, s, pa);
+        pa.tile0 = 0;
+        pa.sums = sums;
+        if (pl.whole > 0)
+            hipLaunchKernelGGL(pk.fn, dim3((unsigned)pl.whole), dim3(pk.threads), 0, s, pa);
+        const unsigned tail = (unsigned)(blocks - pl.whole);
+        if (tail) {
+            pa.tile0 = (int)pl.whole;
+            pa.range = pl.range;
+            pa.part = pa.sums = part;
+            hipLaunchKernelGGL(pk.part_fn, dim3(tail, (unsigned)pl.ranges), dim3(pk.threads), 0, s, pa);
+            hipLaunchKernelGGL(pk.combine_fn, dim3(tail, (unsigned)(pk.tile_m * pk.tile_n / 256)),
+                               dim3(256), 0, s, pa, pl.ranges);
+        }
     }
     const hipError_t he = hipGetLastError();
     if (he != hipSuccess) return set_error(MGEMM_ERR_HIP, "split launch: %s", hipGetErrorString(he));
@@ -1069,8 +1243,10 @@ int32_t split_gemm(const GemmArgs &g, int32_t dtype, hipStream_t s) {
                            (double)round_up(g.k, 256) * FmtBF16::S * FmtBF16::ELEM;
         if (big < 4294967296.0)
             return run_split<FmtBF16>(g, s, w, 1 << 17,
-                                      PairKernel{split_pairs_bf16_pipe_kernel, R_BM, R_BN, R_THREADS,
-                                                 256, R_BLOCK});
+                                      PairKernel{split_pairs_bf16_pipe_kernel<false>, R_BM, R_BN,
+                                                 R_THREADS, 256, R_BLOCK, false, 1.15,
+                                                 split_pairs_bf16_pipe_kernel<true>,
+                                                 split_combine_kernel<R_BM, R_BN, BF16_HI, BF16_LO, false>});
         return run_split<FmtBF16>(g, s, w, 1 << 17,
                                   PairKernel{split_pairs_bf16_kernel, PBM, PBN, 512, KPAD, 1});
     }
@@ -1081,7 +1257,9 @@ int32_t split_gemm(const GemmArgs &g, int32_t dtype, hipStream_t s) {
         if (big >= 4294967296.0)
             return set_error(MGEMM_ERR_NOCONFIG, "split int8: slices of one operand exceed 4 GiB");
         return run_split<FmtI8>(g, s, w, 1 << 14,
-                                PairKernel{split_pairs_i8_pipe_kernel, Q_BM, Q_BN, 256, KPAD, 1});
+                                PairKernel{split_pairs_i8_pipe_kernel<false>, Q_BM, Q_BN, 256, KPAD, 1,
+                                           false, 1.5, split_pairs_i8_pipe_kernel<true>,
+                                           split_combine_kernel<Q_BM, Q_BN, I8_HI, I8_LO, false>});
     }
     if (dtype == MGEMM_SPLIT_FP8) {
         // the pair kernel addresses each operand's slices with 32-bit offsets
@@ -1090,8 +1268,9 @@ int32_t split_gemm(const GemmArgs &g, int32_t dtype, hipStream_t s) {
         if (big >= 4294967296.0)
             return set_error(MGEMM_ERR_NOCONFIG, "split fp8: slices of one operand exceed 4 GiB");
         return run_split<FmtE4M3>(g, s, w, 1 << 17,
-                                  PairKernel{split_pairs_e4m3_kernel, E_BM, E_BN, E_THREADS, KPAD, 1,
-                                             true});
+                                  PairKernel{split_pairs_e4m3_kernel<false>, E_BM, E_BN, E_THREADS, KPAD,
+                                             1, true, 4.3, split_pairs_e4m3_kernel<true>,
+                                             split_combine_kernel<E_BM, E_BN, E4M3_HI, E4M3_LO, true>});
     }
     if (dtype == MGEMM_CRT_INT8) return run_crt(g, s, w);
     return set_error(MGEMM_ERR_NOCONFIG, "split dtype %d is not built", dtype);
