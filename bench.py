@@ -48,7 +48,7 @@ PEAK_INT8_TOPS = 5033.2
 # Measured HBM traffic of the N = 8192 FP64 launch (FETCH_SIZE x 2.0 + WRITE_SIZE x
 # 1.0, the factors a plain copy of known size gives); valid for the kernel as
 # profiled -- to be re-measured whenever the FP64 tile kernel changes.
-TRAFFIC_F64_N8192 = 22.05e9
+TRAFFIC_F64_N8192 = 39.5e9
 
 
 def parse():
@@ -101,8 +101,8 @@ def leg_copy(torch, dev, mib=1024, reps=3):
 
 
 def kernel_name(c: dict) -> str:
-    """The FP64 kernel a registered configuration runs on aligned rows (as the
-    profiler names it)."""
+    """The FP64 kernel a registered configuration named by the caller runs on rows
+    the direct-load kernels take (as the profiler names it)."""
     wgm = 4 if c["waves"] == 8 and c["bm"] >= c["bn"] else 2
     wgn = c["waves"] // wgm
     if c["double_buffer"] == 2:
@@ -699,16 +699,20 @@ def main():
 
     if cfg is not None:
         cfg_used, splits, whole_rows = cfg.as_dict(), 1, n
+        kernel, tile = kernel_name(cfg_used), (cfg_used["bm"], cfg_used["bn"])
     else:
+        # the default runs its plan on a direct-load tile with the configuration's
+        # bits; large squares take the 128 x 128 one
         c, splits, whole_rows = mg.choice(n, n, n, mg.F64, rows=True)
         cfg_used = c.as_dict()
+        kernel, tile = "gemm_direct_kernel<double,128,128,16,2>", (128, 128)
     if splits == 1:
-        launches = kernel_name(cfg_used) + " (one launch per step)"
+        launches = kernel + " (one launch per step)"
     elif whole_rows == 0:
-        launches = (f"split-k of {kernel_name(cfg_used)}, k in {splits} ranges, and the sum of "
+        launches = (f"split-k of {kernel}, k in {splits} ranges, and the sum of "
                     "the planes (two launches per step; kernel_avg_ms is their total)")
     else:
-        launches = (f"{kernel_name(cfg_used)} on the first {whole_rows} rows, its split-k on "
+        launches = (f"{kernel} on the first {whole_rows} rows, its split-k on "
                     f"the other {n - whole_rows} rows with k in {splits} ranges, and the sum of "
                     "the planes (three launches per step; kernel_avg_ms is their total)")
     out = {
@@ -741,16 +745,16 @@ def main():
                      "peak": PEAK_F64_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(flops / (kern_ms * 1e-3) / 1e12 / PEAK_F64_TFLOPS, 4),
                      # HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE runs in
-                     # profiles/gemm_pipe_f64_N8192_traffic.md (copy-calibrated)
+                     # profiles/gemm_direct_f64_N8192_traffic_and_busy.md (copy-calibrated)
                      "traffic": TRAFFIC_F64_N8192 if n == 8192 and cfg is None else None,
                      "traffic_unit": "bytes per launch",
                      "kernel": launches,
                      "kernel_avg_ms": round(kern_ms, 4),
                      "work_per_launch": f"2*N^3 = {flops:.4g} FLOP",
-                     # Eq. 6 for the kernel's 256 x 128 tiles: the bytes with no cache
+                     # Eq. 6 for the kernel's tiles: the bytes with no cache
                      # reuse, against the algorithmic minimum (A, B, C read, C written)
                      "traffic_model": {"tiles_no_reuse": pm.tile_traffic_bytes(
-                                           n, n, n, cfg_used["bm"], cfg_used["bn"], 8),
+                                           n, n, n, *tile, 8),
                                        "algorithmic": 4.0 * 8 * n * n}},
         "cpu_baseline": cpu,
     }

@@ -12,10 +12,10 @@
 //                            bucket (grid = resident work-groups of the whole
 //                            GPU) that pulls tiles from atomic counters; the
 //                            default runs one work-group per tile with
-//                            direct-load 64 x 64 tiles (direct.hip).  A
-//                            counter-reset kernel and the bucket kernels (as
-//                            parallel branches) are captured once into a HIP
-//                            graph; executing the plan is one hipGraphLaunch.
+//                            direct-load 64 x 64 tiles (direct.hip).  That
+//                            one launch, or a counter-reset kernel and the
+//                            bucket kernels (as parallel branches), are captured
+//                            once into a HIP graph; executing the plan is one hipGraphLaunch.
 //                            Each tile sums k in the order of gemm_ex with the
 //                            same configuration, so results are bitwise
 //                            identical to per-problem gemm_ex calls.

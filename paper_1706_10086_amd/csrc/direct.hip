@@ -17,7 +17,7 @@ namespace mgemm {
 // Two stages of 18-36 KB leave room for two to eight work-groups per compute unit,
 // whose products fill each other's barriers, prologues and epilogues: with FP64
 // 1999 x 1501 x 2777 (odd rows) the two-stage register-staged 64 x 64 x 32 tile ran
-// at 37.6 TFLOP/s, this 64 x 64 x 16 tile at 60.
+// at 37.6 TFLOP/s, this 64 x 64 x 16 tile at 62.
 template <typename T, int BM, int BN, int BK, int OCC>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC)))
 gemm_direct_kernel(GemmArgs p, int64_t kc, T *W) {

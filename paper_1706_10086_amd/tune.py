@@ -159,8 +159,8 @@ GRID_EPT = (4, 8, 16)
 GRID_DBUF = (0, 1)
 GRID_OCC = (1, 2)
 # the hand-registered kernels also use k-steps of 16 and runs of 2 elements (one
-# 16-byte FP64 load): a 256 x 128 FP64 tile with three stages fits the LDS only
-# at bk = 16
+# 16-byte FP64 load): a 256 x 128 FP64 direct-load tile of three stages, the form the
+# selection was made for, fits the LDS only at bk = 16
 EXT_BK = (16,)
 EXT_EPT = (2,)
 LDS_BYTES = 160 * 1024          # per compute unit
@@ -197,8 +197,9 @@ def wave_layout(bm: int, bn: int, waves: int):
 def lds_bytes(dtype: int, bm: int, bn: int, bk: int, dbuf: int) -> int:
     """LDS one work-group needs: the two-stage kernel's padded A and B tiles (A
     rows bk + 2, B rows bn + 8 FP64 / + 16 FP32 elements) per stage (dbuf 0, 1:
-    one, two stages); the three-stage kernel's 16-byte units (A rows one unit
-    longer, B rows 4 FP64 / 2 FP32 units longer) times three (dbuf 2)."""
+    one, two stages); the direct-load kernel's 16-byte units (A rows one unit
+    longer, B rows 4 FP64 / 2 FP32 units longer) times the three stages it was
+    selected with (dbuf 2; it runs with two)."""
     S = 4 if dtype == F32 else 8
     if dbuf == 2:
         au = bk * S // 16 + 1
@@ -544,7 +545,7 @@ def refine(shapes, dtype: int, db: DB, top: int = 8, min_ms: float = 2.0, max_re
 # ---------------------------------------------------------------------------
 def batch_rules(dtype: int) -> dict:
     """Candidate rules, each mapping a problem (m, n, k) to a configuration tuple:
-    one registered configuration for every problem (three-stage entries are left
+    one registered configuration for every problem (direct-load entries are left
     out: in a plan they run their two-stage fallback, registered on its own), and
     mixtures of the 64 x 64 four-wave tile with the smallest tile for thin
     problems (min(m, n) <= T) or a 128 x 128 tile for large ones (min(m, n) >= T)."""
