@@ -56,6 +56,7 @@ struct Bucket {
     bool use_map = false;
     std::vector<uint64_t> map;        // the lists' entries, list after list (host copy)
     std::vector<int64_t> list_off;    // list l holds [list_off[l], list_off[l+1])
+    int64_t longest = 0;              // entries of the longest list (if use_map)
 };
 
 // Tile maps are built while every bucket's map fits this many bytes in total and
@@ -376,9 +377,15 @@ int32_t gemm_batched_plan_create(int64_t count, const int64_t *m, const int64_t 
             if (fits && map_bytes <= TILE_MAP_MAX_BYTES) {
                 b.use_map = true;
                 build_lists(b);
+                // one work-group per tile only while their work-items fit a grid (2^24
+                // tiles): more tiles stay with the persistent kernel
+                for (size_t l = 0; l + 1 < b.list_off.size(); ++l)
+                    b.longest = std::max(b.longest, b.list_off[l + 1] - b.list_off[l]);
+                b.direct = b.direct && grid_fits(b.longest * BATCH_LISTS, DIRECT_THREADS);
                 b.map_offset = bytes;
                 bytes += (b.map.size() * sizeof(uint64_t) + 255) / 256 * 256;
             } else {
+                b.direct = false;
                 b.list_off = {0, b.total_tiles};
             }
             b.list_offset = bytes;
@@ -417,7 +424,7 @@ int32_t gemm_batched_plan_create(int64_t count, const int64_t *m, const int64_t 
     // capture: reset counters, then every bucket kernel on its own branch; one bucket
     // that the direct-load kernel runs is one launch (it counts nothing, and the reset
     // took 4.4 us of every execution: 109 FP64 products of 16-256 25.7 and 21.5 us)
-    const bool one = nb == 1 && p->buckets[0].direct && p->buckets[0].use_map;
+    const bool one = nb == 1 && p->buckets[0].direct;
     hipStream_t cs = nullptr;
     std::vector<hipStream_t> branch(nb, nullptr);
     std::vector<hipEvent_t> done(nb, nullptr);
@@ -441,13 +448,10 @@ int32_t gemm_batched_plan_create(int64_t count, const int64_t *m, const int64_t 
             const hipStream_t bs = one ? cs : branch[b];
             if (!one) ge = hipStreamWaitEvent(bs, start, 0);
             if (ge != hipSuccess && rc == 0) rc = hip_fail(ge, "plan: capture fork");
-            int64_t longest = 0;
-            for (size_t l = 0; l + 1 < bk.list_off.size(); ++l)
-                longest = std::max(longest, bk.list_off[l + 1] - bk.list_off[l]);
-            hipError_t le = bk.direct && bk.use_map ? launch_batched_direct(
+            hipError_t le = bk.direct ? launch_batched_direct(
                 dtype, (const BatchProblem *)(p->dev + bk.offset),
                 (const uint64_t *)(p->dev + bk.map_offset),
-                (const int64_t *)(p->dev + bk.list_offset), longest, bs) : bk.entry->batched(
+                (const int64_t *)(p->dev + bk.list_offset), bk.longest, bs) : bk.entry->batched(
                 (const BatchProblem *)(p->dev + bk.offset),
                 bk.use_map ? (const uint64_t *)(p->dev + bk.map_offset) : nullptr,
                 (const int64_t *)(p->dev + bk.list_offset), (int)bk.list_off.size() - 1,

@@ -44,7 +44,7 @@ template <typename T, int BM, int BN, int BK, int OCC>
 static hipError_t launch_direct(const GemmArgs &a, int S, int64_t kc, void *W, hipStream_t s) {
     const int64_t blocks = ((a.m + BM - 1) / BM) * ((a.n + BN - 1) / BN);
     if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffff || S < 1 || S > 65535) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, DIRECT_THREADS) || S < 1 || S > 65535) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((gemm_direct_kernel<T, BM, BN, BK, OCC>), dim3((unsigned)blocks, (unsigned)S),
                        dim3(256), 0, s, a, kc, (T *)W);
     return hipGetLastError();
@@ -53,8 +53,6 @@ static hipError_t launch_direct(const GemmArgs &a, int S, int64_t kc, void *W, h
 // Several whole products in one launch, described in the kernel's arguments (no copy
 // to the device, nothing kept between calls): work-group b runs a tile of the problem
 // whose tiles start at or before b.
-constexpr int LIST_MAX = 56;                  // arguments below 4 KiB
-
 struct ListProblem {
     const void *A, *B;
     void *C;
@@ -96,7 +94,7 @@ static hipError_t launch_list(const GemmArgs *p, int count, hipStream_t s) {
                   (int32_t)g.lda, (int32_t)g.ldb, (int32_t)g.ldc};
         tiles += ((g.m + BM - 1) / BM) * ((g.n + BN - 1) / BN);
     }
-    if (tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
+    if (!grid_fits(tiles, DIRECT_THREADS)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((gemm_list_kernel<T, BM, BN, BK, OCC>), dim3((unsigned)tiles), dim3(256), 0,
                        s, a);
     return hipGetLastError();
@@ -159,7 +157,9 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
     const DirectTile *best = nullptr;
     double tb = 0.0;
     for (int i = 0; i < cnt; ++i) {
-        if (!t[i].eligible(a)) continue;
+        if (!t[i].eligible(a) ||
+            !grid_fits(((a.m + t[i].bm - 1) / t[i].bm) * ((a.n + t[i].bn - 1) / t[i].bn), DIRECT_THREADS))
+            continue;
         const double ti = direct_time(t[i], a.m, a.n, kc, S, cus > 0 ? cus : 256);
         if (!best || ti < tb) {
             best = &t[i];
@@ -170,8 +170,8 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
     return best ? best->launch(a, S, kc, W, s) : hipSuccess;
 }
 
-// Rows and tiles of one list launch in 32 bits for every tile of the table; beyond
-// LIST_FLOPS (tens of microseconds alone) a product gains nothing from company and
+// Rows of one list launch in 32 bits for every tile of the table, and its work-items
+// (of many products of a few columns) in 32 bits on the smallest one; beyond LIST_FLOPS (tens of microseconds alone) a product gains nothing from company and
 // takes its own tile.
 constexpr double LIST_FLOPS = 4e9;
 
@@ -179,7 +179,7 @@ bool list_eligible(const GemmArgs &a, int32_t dtype) {
     const int64_t es = (int64_t)elem_size(dtype), lim = (int64_t)1 << 31;
     return a.m >= 1 && a.k >= 1 && a.n >= 16 / es && ((uintptr_t)a.A % 4) == 0 &&
            ((uintptr_t)a.B % 4) == 0 && a.m < lim && a.k < lim && 128 * a.lda * es < lim &&
-           (64 * a.ldb + 128) * es < lim && a.ldc < lim &&
+           (64 * a.ldb + 128) * es < lim && a.ldc < lim && list_grid_fits(a.m, a.n) &&
            2.0 * (double)a.m * (double)a.n * (double)a.k <= LIST_FLOPS;
 }
 
@@ -253,7 +253,7 @@ hipError_t launch_batched_direct(int32_t dtype, const BatchProblem *probs, const
                                  const int64_t *off, int64_t longest, hipStream_t s) {
     const int64_t blocks = longest * BATCH_LISTS;
     if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, DIRECT_THREADS)) return hipErrorInvalidConfiguration;
     if (dtype == MGEMM_F32)
         hipLaunchKernelGGL((gemm_batched_direct_kernel<float, 64, 64, 32, 3>),
                            dim3((unsigned)blocks), dim3(256), 0, s, probs, map, off);

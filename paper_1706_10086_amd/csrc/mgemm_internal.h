@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "host_rules.h"
 #include "mgemm.h"
 
 namespace mgemm {
