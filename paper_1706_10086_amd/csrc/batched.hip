@@ -23,6 +23,7 @@
 #include <map>
 #include <new>
 #include <set>
+#include <string>
 #include <utility>
 #include <vector>
 
@@ -137,28 +138,6 @@ static int32_t hip_fail(hipError_t e, const char *what) {
 // window to run in turn.
 constexpr int64_t LIST_WINDOW = 1024;
 
-struct Span {
-    uintptr_t b, e;
-    bool write;
-};
-
-static void add_span(std::vector<Span> &v, const void *p, int64_t r, int64_t c, int64_t ld, size_t es,
-                     bool write) {
-    v.push_back({(uintptr_t)p, (uintptr_t)p + (size_t)((r - 1) * ld + c) * es, write});
-}
-
-// Whether a written span meets any other span.
-static bool written_twice_or_read(std::vector<Span> &v) {
-    std::sort(v.begin(), v.end(), [](const Span &x, const Span &y) { return x.b < y.b; });
-    uintptr_t any_end = 0, write_end = 0;        // furthest ends so far
-    for (const Span &s : v) {
-        if (s.b < (s.write ? any_end : write_end)) return true;
-        any_end = std::max(any_end, s.e);
-        if (s.write) write_end = std::max(write_end, s.e);
-    }
-    return false;
-}
-
 // gemm_batched on checked arguments.
 static int32_t batched_run(int64_t count, const int64_t *m, const int64_t *n, const int64_t *k,
                            const double *alpha, const void *const *A, const int64_t *lda,
@@ -166,6 +145,9 @@ static int32_t batched_run(int64_t count, const int64_t *m, const int64_t *n, co
                            void *const *C, const int64_t *ldc, int32_t dtype) {
     const hipStream_t s = current_stream();
     const bool may_launch = dtype <= MGEMM_F32 && !capturing(s);
+    auto args = [&](int64_t i) {
+        return GemmArgs{m[i], n[i], k[i], alpha[i], beta[i], A[i], lda[i], B[i], ldb[i], C[i], ldc[i]};
+    };
     std::vector<GemmArgs> group;
     std::vector<Span> spans;
     for (int64_t i0 = 0; i0 < count; i0 += LIST_WINDOW) {
@@ -183,38 +165,36 @@ static int32_t batched_run(int64_t count, const int64_t *m, const int64_t *n, co
             }
             shared = !written_twice_or_read(spans);
         }
-        group.clear();
-        for (int64_t i = i0; i < i1; ++i) {
-            const GemmArgs a{m[i], n[i], k[i], alpha[i], beta[i], A[i], lda[i], B[i], ldb[i], C[i], ldc[i]};
-            if (shared && a.m > 0 && a.n > 0 && a.k > 0 && a.alpha != 0.0) {
-                CallPlan cp;
-                int32_t rc = plan_call(a, dtype, nullptr, may_launch, cp);
-                if (rc) return rc;
-                if (!cp.named && cp.sp.S == 1 && list_eligible(a, dtype)) {
-                    group.push_back(a);
-                    continue;
-                }
-                rc = run_plan(cp, a, dtype, s);
-                if (rc) return rc;
-                continue;
-            }
-            int32_t rc = gemm_ex(m[i], n[i], k[i], alpha[i], A[i], lda[i], B[i], ldb[i], beta[i],
-                                 C[i], ldc[i], dtype, nullptr, nullptr);
-            if (rc) return rc;
-        }
-        if (group.empty()) continue;
-        if (group.size() == 1) {
+        auto run = [&](int64_t i, bool *joins) -> int32_t {
+            const GemmArgs a = args(i);
+            if (!shared || a.m == 0 || a.n == 0 || a.k == 0 || a.alpha == 0.0)
+                return gemm_ex(a.m, a.n, a.k, a.alpha, a.A, a.lda, a.B, a.ldb, a.beta, a.C, a.ldc, dtype,
+                               nullptr, nullptr);
             CallPlan cp;
-            int32_t rc = plan_call(group[0], dtype, nullptr, may_launch, cp);
-            if (rc == 0) rc = run_plan(cp, group[0], dtype, s);
+            const int32_t rc = plan_call(a, dtype, nullptr, may_launch, cp);
             if (rc) return rc;
-            continue;
-        }
-        std::stable_sort(group.begin(), group.end(),
-                         [](const GemmArgs &x, const GemmArgs &y) { return x.k > y.k; });
-        const hipError_t he =
-            run_direct_list(group.data(), (int64_t)group.size(), dtype, compute_units(), s);
-        if (he != hipSuccess) return hip_fail(he, "batched launch");
+            *joins = !cp.named && cp.sp.S == 1 && list_eligible(a, dtype);
+            return *joins ? 0 : run_plan(cp, a, dtype, s);
+        };
+        auto run_group = [&](const std::vector<int64_t> &g) -> int32_t {
+            if (g.size() == 1) {
+                const GemmArgs a = args(g[0]);
+                CallPlan cp;
+                const int32_t rc = plan_call(a, dtype, nullptr, may_launch, cp);
+                return rc ? rc : run_plan(cp, a, dtype, s);
+            }
+            group.clear();
+            for (int64_t i : g) group.push_back(args(i));
+            std::stable_sort(group.begin(), group.end(),
+                             [](const GemmArgs &x, const GemmArgs &y) { return x.k > y.k; });
+            const hipError_t he =
+                run_direct_list(group.data(), (int64_t)group.size(), dtype, compute_units(), s);
+            return he == hipSuccess ? 0 : hip_fail(he, "batched launch");
+        };
+        std::string message;
+        const int32_t rc = run_window(i0, i1, run, run_group,
+                                      [&] { message = mgemm_last_error(); });
+        if (rc) return message.empty() ? rc : set_error(rc, "%s", message.c_str());
     }
     return 0;
 }

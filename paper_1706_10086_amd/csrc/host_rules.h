@@ -2,7 +2,11 @@
 // and check the rules on the CPU.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <vector>
 
 namespace mgemm {
 
@@ -20,6 +24,53 @@ constexpr int LIST_MAX = 56;
 inline bool list_grid_fits(int64_t m, int64_t n) {
     const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32);
     return grid_fits(tiles * LIST_MAX, DIRECT_THREADS);
+}
+
+// ---------------------------------------------------------------------------
+// Lists whose products share launches.
+// ---------------------------------------------------------------------------
+// Bytes that a product of a list reads or writes.
+struct Span {
+    uintptr_t b, e;
+    bool write;
+};
+
+inline void add_span(std::vector<Span> &v, const void *p, int64_t r, int64_t c, int64_t ld, size_t es,
+                     bool write) {
+    v.push_back({(uintptr_t)p, (uintptr_t)p + (size_t)((r - 1) * ld + c) * es, write});
+}
+
+// Whether a written span meets any other span.
+inline bool written_twice_or_read(std::vector<Span> &v) {
+    std::sort(v.begin(), v.end(), [](const Span &x, const Span &y) { return x.b < y.b; });
+    uintptr_t any_end = 0, write_end = 0;        // furthest ends so far
+    for (const Span &s : v) {
+        if (s.b < (s.write ? any_end : write_end)) return true;
+        any_end = std::max(any_end, s.e);
+        if (s.write) write_end = std::max(write_end, s.e);
+    }
+    return false;
+}
+
+// Runs products [i0, i1) of a list, which do not depend on each other: run(i, &joins)
+// runs product i or sets joins, and the products that joined run together at the end.
+// Where one fails, those before it -- the joined ones too -- still run, as in a list
+// run in turn; failed() is called before them, for the error's message.
+template <typename Run, typename RunGroup, typename Failed>
+int32_t run_window(int64_t i0, int64_t i1, Run run, RunGroup run_group, Failed failed) {
+    std::vector<int64_t> group;
+    int32_t rc = 0;
+    for (int64_t i = i0; i < i1 && rc == 0; ++i) {
+        bool joins = false;
+        rc = run(i, &joins);
+        if (rc == 0 && joins) group.push_back(i);
+    }
+    if (rc) failed();
+    if (!group.empty()) {
+        const int32_t grc = run_group(group);
+        if (rc == 0) rc = grc;
+    }
+    return rc;
 }
 
 }  // namespace mgemm

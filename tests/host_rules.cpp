@@ -9,4 +9,33 @@ int grid_fits_c(int64_t blocks, int64_t threads) { return grid_fits(blocks, thre
 
 int list_grid_fits_c(int64_t m, int64_t n) { return list_grid_fits(m, n); }
 
+// Spans [b, e) of a list, each with a flag for written ones.
+int dependent_c(int count, const int64_t *b, const int64_t *e, const int32_t *write) {
+    std::vector<Span> v;
+    for (int i = 0; i < count; ++i)
+        add_span(v, (const void *)(uintptr_t)b[i], 1, e[i] - b[i], e[i] - b[i], 1, write[i] != 0);
+    return written_twice_or_read(v);
+}
+
+// Products 0..count-1 with what they do (0: run alone, 1: join, < 0: fail with that
+// code); `order` receives them as they run, `*told` how many had run when the failure
+// was told.  group_rc: what the joined products' launch returns.
+int window_c(int count, const int32_t *what, int group_rc, int32_t *order, int *ran, int *told) {
+    *ran = 0;
+    *told = -1;
+    return run_window(
+        0, count,
+        [&](int64_t i, bool *joins) -> int32_t {
+            if (what[i] < 0) return what[i];
+            *joins = what[i] == 1;
+            if (!*joins) order[(*ran)++] = (int32_t)i;
+            return 0;
+        },
+        [&](const std::vector<int64_t> &g) -> int32_t {
+            for (int64_t i : g) order[(*ran)++] = (int32_t)i;
+            return group_rc;
+        },
+        [&] { *told = *ran; });
+}
+
 }  // extern "C"

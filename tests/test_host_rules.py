@@ -1,6 +1,8 @@
 """The host side's rules that need no GPU (csrc/host_rules.h), compiled alone with the
-host compiler: which grids a launch may take."""
+host compiler: which grids a launch may take, which lists' products depend on each
+other, and what of a list runs when one of its products fails."""
 import ctypes
+import itertools
 import os
 import subprocess
 
@@ -37,3 +39,50 @@ def test_a_full_list_of_the_largest_products_fits_a_grid(R):
     # the same count in two dimensions, and sizes at a tile's edge
     assert R.list_grid_fits_c(32 * most - 31, 32) and not R.list_grid_fits_c(32 * most + 1, 1)
     assert R.list_grid_fits_c(1024, 1024) and not R.list_grid_fits_c(1 << 27, 4)
+
+
+def dependent(R, spans):
+    n = len(spans)
+    b, e = ((ctypes.c_int64 * n)(*[s[i] for s in spans]) for i in (0, 1))
+    w = (ctypes.c_int32 * n)(*[int(s[2]) for s in spans])
+    return bool(R.dependent_c(n, b, e, w))
+
+
+def test_dependent_products_are_found(R):
+    """Against every pair: a written span that meets another one, in any order of the
+    list, at shared and touching ends and with one inside the other."""
+    cuts = [0, 4, 5, 8, 9, 12]
+    spans = [(a, b, w) for a, b in itertools.combinations(cuts, 2) for w in (False, True)]
+    meets = lambda x, y: x[0] < y[1] and y[0] < x[1]  # noqa: E731
+    seen = set()
+    for some in itertools.permutations(spans, 3):
+        want = any(meets(x, y) and (x[2] or y[2]) for x, y in itertools.combinations(some, 2))
+        assert dependent(R, some) == want, some
+        seen.add(want)
+    assert seen == {True, False}
+    assert not dependent(R, [(0, 4, True)]) and not dependent(R, [(0, 4, False)] * 5)
+
+
+def window(R, what, group_rc=0):
+    n = len(what)
+    order = (ctypes.c_int32 * n)()
+    ran, told = ctypes.c_int(), ctypes.c_int()
+    rc = R.window_c(n, (ctypes.c_int32 * n)(*what), group_rc, order, ctypes.byref(ran),
+                    ctypes.byref(told))
+    return rc, list(order[:ran.value]), told.value
+
+
+@pytest.mark.parametrize("what,group_rc,rc,ran,told", [
+    ([0, 1, 0, 1, 1], 0, 0, [0, 2, 1, 3, 4], -1),
+    ([1, 1], 0, 0, [0, 1], -1),
+    ([0, 0], 0, 0, [0, 1], -1),
+    # a failure leaves what came before it done and what comes after it undone
+    ([1, 0, 1, -7, 1, 0], 0, -7, [1, 0, 2], 1),
+    ([1, -3], 0, -3, [0], 0),
+    ([-3, 1, 0], 0, -3, [], 0),
+    # the first error is the one reported
+    ([1, 0, -7], -9, -7, [1, 0], 1),
+    ([1, 0], -9, -9, [1, 0], -1),
+])
+def test_a_failing_product_leaves_the_ones_before_it_done(R, what, group_rc, rc, ran, told):
+    assert window(R, what, group_rc) == (rc, ran, told)
