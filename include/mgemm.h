@@ -274,7 +274,8 @@ MGEMM_API int32_t mlp_set_data(void *mlp, int64_t rows, const float *X, const fl
  * without an update. */
 MGEMM_API int32_t mlp_loss_grad(void *mlp, float *loss, float *grad);
 /* steps full-batch Adam steps (two kernels per step for networks of at most 32
- * inputs and 128 hidden units, else one captured HIP graph per step); *last_loss
+ * inputs and 128 hidden units, but for many outputs on few rows, else one captured HIP
+ * graph per step); *last_loss
  * (host, may be NULL) receives the loss evaluated in the last step. */
 MGEMM_API int32_t mlp_train(void *mlp, int32_t steps, float lr, float beta1, float beta2,
                             float eps, float *last_loss);

@@ -73,4 +73,32 @@ int32_t run_window(int64_t i0, int64_t i1, Run run, RunGroup run_group, Failed f
     return rc;
 }
 
+// ---------------------------------------------------------------------------
+// Which networks train on the step kernel.
+// ---------------------------------------------------------------------------
+constexpr int STEP_MAX_IN = 32, STEP_MAX_HIDDEN = 128;
+
+// Training rows per tile of the step kernel.
+inline int step_rows(int hidden) { return hidden <= 64 ? 64 : 32; }
+
+// Work-groups of the step kernel for a network and a training set (at most one per
+// compute unit): 0 where the step runs layer by layer instead.
+//
+// A work-group takes the outputs 64 at a time, and the layer-by-layer path spreads them
+// over the GPU, so of many outputs the step kernel needs many rows: a step of 64 hidden
+// units on 64 rows takes 42 us against 74 layer by layer with 247 outputs, 108 against
+// 108 with 1024, 381 against 249 with 4096 (with 13600 rows 459 against 864).  Above 64
+// hidden units a work-group that takes a second tile of 32 rows reads and rewrites its
+// whole gradient share, which costs as much as it saves once rounds x outputs passes
+// about 4000: 128 hidden units, 13600 rows (two rounds) 124 against 233 us with 247
+// outputs, 318 against 396 with 1024, 665 against 630 with 2048; 60000 rows (eight) 470
+// against 557 with 247, 766 against 754 with 512, 1349 against 1252 with 1024.
+inline int step_blocks(int in, int hidden, int out, int64_t rows, int cus) {
+    if (in > STEP_MAX_IN || hidden > STEP_MAX_HIDDEN || cus < 1) return 0;
+    const int64_t tiles = (rows + step_rows(hidden) - 1) / step_rows(hidden);
+    if (out > 768 && rows < out) return 0;
+    if (hidden > 64 && (tiles + cus - 1) / cus * out > 2048) return 0;
+    return (int)std::min<int64_t>(tiles, cus);
+}
+
 }  // namespace mgemm

@@ -7,8 +7,8 @@
 //
 // Parameters are one flat FP32 vector W1, b1, W2, b2, W3, b3 (row-major).  The
 // training set (rows of x, targets t, mask M) lives on the device.  Networks of at
-// most 32 inputs and 128 hidden units train with two kernels a step (mlp_step.h);
-// for wider ones a step (forward, loss, backward, Adam) runs layer by layer, captured
+// most 32 inputs and 128 hidden units train with two kernels a step (mlp_step.h) but
+// for many outputs on few rows (host_rules.h: step_blocks); for the others a step (forward, loss, backward, Adam) runs layer by layer, captured
 // once into a HIP graph and replayed per step.  The linear layers' products (forward,
 // the backward products and the weight gradients) run on the matrix cores in FP32;
 // every reduction runs in a fixed order, so training is deterministic.
@@ -340,18 +340,14 @@ static void free_data(Mlp *p) {
     p->blocks = 0;
 }
 
-// Blocks of the step kernel for a training set of `rows` rows (0: the network is too
-// wide for it): one per tile of rows, at most one per compute unit.
-static int step_rows(const Mlp *p) { return p->H <= 64 ? 64 : 32; }
-
+// Blocks of the step kernel for a training set of `rows` rows (0: layer by layer).
 static int step_blocks(const Mlp *p, int64_t rows) {
-    if (p->I > STEP_MAX_IN || p->H > STEP_MAX_HIDDEN) return 0;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         cus = 256;
-    return (int)std::min<int64_t>((rows + step_rows(p) - 1) / step_rows(p), cus);
+    return step_blocks(p->I, p->H, p->O, rows, cus);
 }
 
 // Elements of one block's gradient share.
@@ -364,7 +360,7 @@ static void step_launch(Mlp *p, hipStream_t s, float lr, float b1, float b2, flo
     const int64_t plane = share_elems(p);
     const MlpStepArgs a{p->I, p->H, p->O, p->B, p->X, p->T, p->M, p->par, p->planes, plane, p->part,
                         lr > 0.0f ? p->step : (int *)nullptr};
-    if (step_rows(p) == 64)
+    if (step_rows(p->H) == 64)
         hipLaunchKernelGGL((mlp_step_kernel<64, 64>), dim3(p->blocks), dim3(512), 0, s, a);
     else
         hipLaunchKernelGGL((mlp_step_kernel<128, 32>), dim3(p->blocks), dim3(512), 0, s, a);
@@ -489,6 +485,33 @@ static void mlp_grad_launch(Mlp *p, hipStream_t s, bool count_step) {
     grad_product(p, p->dz1, H, p->X, I, nullptr, p->gW1(), p->gb1(), s);
 }
 
+// The buffers of a training set of B rows, trained by `blocks` blocks of the step kernel
+// (which keeps no activations) or, with 0, layer by layer.
+static int32_t alloc_data(Mlp *p, int64_t B, int blocks) {
+    const bool whole = blocks == 0;
+    const int64_t tiles3 = ((B + MM_T - 1) / MM_T) * ((p->O + MM_T - 1) / MM_T);
+    p->B = B;    // reset below on failure
+    p->blocks = blocks;
+    struct { float **dst; int64_t n; } bufs[] = {
+        {&p->X, B * p->I}, {&p->T, B * p->O}, {&p->M, B * p->O}, {&p->z1, whole ? B * p->H : 0},
+        {&p->h1, whole ? B * p->H : 0}, {&p->z2, whole ? B * p->H : 0},
+        {&p->h2, whole ? B * p->H : 0}, {&p->y, whole ? B * p->O : 0},
+        {&p->d, whole ? B * p->O : 0}, {&p->dz2, whole ? B * p->H : 0},
+        {&p->dz1, whole ? B * p->H : 0},
+        {&p->planes, whole ? planes_elems(p, B) : blocks * share_elems(p)},
+        {&p->part, whole ? 2 * tiles3 : 2 * (int64_t)blocks}};
+    for (auto &b : bufs) {
+        if (b.n == 0) continue;
+        if (hipMalloc((void **)b.dst, (size_t)b.n * sizeof(float)) != hipSuccess) {
+            (void)hipGetLastError();
+            *b.dst = nullptr;
+            free_data(p);
+            return set_error(MGEMM_ERR_NOMEM, "mlp: training buffers for %lld rows", (long long)B);
+        }
+    }
+    return 0;
+}
+
 static int32_t hip_err(hipError_t e, const char *w) {
     return set_error(MGEMM_ERR_HIP, "%s: %s", w, hipGetErrorString(e));
 }
@@ -572,28 +595,10 @@ int32_t mlp_set_data(void *handle, int64_t rows, const float *X, const float *T,
     if (se != hipSuccess) return hip_err(se, "mlp_set_data");
     free_data(p);
     const int64_t B = rows;
-    const int64_t tiles3 = ((B + MM_T - 1) / MM_T) * ((p->O + MM_T - 1) / MM_T);
-    p->B = B;    // for planes_elems; reset below on failure
-    const int blocks = step_blocks(p, B);
-    p->blocks = blocks;
-    const bool whole = blocks == 0;     // the step kernel keeps no activations
-    struct { float **dst; int64_t n; } bufs[] = {
-        {&p->X, B * p->I}, {&p->T, B * p->O}, {&p->M, B * p->O}, {&p->z1, whole ? B * p->H : 0},
-        {&p->h1, whole ? B * p->H : 0}, {&p->z2, whole ? B * p->H : 0},
-        {&p->h2, whole ? B * p->H : 0}, {&p->y, whole ? B * p->O : 0},
-        {&p->d, whole ? B * p->O : 0}, {&p->dz2, whole ? B * p->H : 0},
-        {&p->dz1, whole ? B * p->H : 0},
-        {&p->planes, whole ? planes_elems(p, B) : blocks * share_elems(p)},
-        {&p->part, whole ? 2 * tiles3 : 2 * (int64_t)blocks}};
-    for (auto &b : bufs) {
-        if (b.n == 0) continue;
-        if (hipMalloc((void **)b.dst, (size_t)b.n * sizeof(float)) != hipSuccess) {
-            (void)hipGetLastError();
-            *b.dst = nullptr;
-            free_data(p);
-            return set_error(MGEMM_ERR_NOMEM, "mlp: training buffers for %lld rows", (long long)rows);
-        }
-    }
+    // the step kernel's gradient shares may not fit where the activations do
+    int32_t rc = alloc_data(p, B, step_blocks(p, B));
+    if (rc && step_blocks(p, B)) rc = alloc_data(p, B, 0);
+    if (rc) return rc;
     hipError_t e = hipMemcpy(p->X, X, (size_t)B * p->I * sizeof(float), hipMemcpyDeviceToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->T, T, (size_t)B * p->O * sizeof(float), hipMemcpyDeviceToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->M, M, (size_t)B * p->O * sizeof(float), hipMemcpyDeviceToDevice);

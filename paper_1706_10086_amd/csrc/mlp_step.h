@@ -8,10 +8,10 @@
 
 namespace mgemm {
 
-// Networks the step kernel holds in LDS: hidden width padded to HP = 64 (tiles of
-// 64 rows) or 128 (32 rows), at most STEP_MAX_IN inputs, any number of outputs (in
-// chunks of 64).
-constexpr int STEP_MAX_IN = 32, STEP_MAX_HIDDEN = 128, STEP_CHUNK = 64;
+// The step kernel holds networks of at most STEP_MAX_IN inputs and STEP_MAX_HIDDEN
+// hidden units (host_rules.h) in LDS: hidden width padded to HP = 64 (tiles of 64 rows)
+// or 128 (32 rows), any number of outputs (in chunks of 64).
+constexpr int STEP_CHUNK = 64;
 
 struct MlpStepArgs {
     int I, H, O;

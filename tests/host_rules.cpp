@@ -9,6 +9,10 @@ int grid_fits_c(int64_t blocks, int64_t threads) { return grid_fits(blocks, thre
 
 int list_grid_fits_c(int64_t m, int64_t n) { return list_grid_fits(m, n); }
 
+int step_blocks_c(int in, int hidden, int out, int64_t rows, int cus) {
+    return step_blocks(in, hidden, out, rows, cus);
+}
+
 // Spans [b, e) of a list, each with a flag for written ones.
 int dependent_c(int count, const int64_t *b, const int64_t *e, const int32_t *write) {
     std::vector<Span> v;

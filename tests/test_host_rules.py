@@ -1,6 +1,7 @@
 """The host side's rules that need no GPU (csrc/host_rules.h), compiled alone with the
 host compiler: which grids a launch may take, which lists' products depend on each
-other, and what of a list runs when one of its products fails."""
+other, what of a list runs when one of its products fails, and which networks train on
+the step kernel."""
 import ctypes
 import itertools
 import os
@@ -21,6 +22,8 @@ def R(tmp_path_factory):
     i64 = ctypes.c_int64
     lib.grid_fits_c.argtypes = [i64, i64]
     lib.list_grid_fits_c.argtypes = [i64, i64]
+    i32 = ctypes.c_int
+    lib.step_blocks_c.argtypes = [i32, i32, i32, i64, i32]
     return lib
 
 
@@ -86,3 +89,20 @@ def window(R, what, group_rc=0):
 ])
 def test_a_failing_product_leaves_the_ones_before_it_done(R, what, group_rc, rc, ran, told):
     assert window(R, what, group_rc) == (rc, ran, told)
+
+
+@pytest.mark.parametrize("dims,rows,blocks", [
+    # the tile-choice network, the smallest sets, one tile of rows more
+    ((6, 64, 247), 13600, 213), ((6, 64, 247), 1, 1), ((6, 64, 247), 65, 2), ((6, 100, 247), 65, 3),
+    ((6, 64, 247), 1 << 20, 256), ((32, 128, 247), 500, 16), ((6, 64, 768), 1, 1),
+    # many outputs on few rows (times at host_rules.h), and rows enough for them
+    ((6, 64, 769), 768, 0), ((6, 64, 769), 769, 13), ((6, 64, 4096), 4095, 0),
+    ((6, 64, 4096), 13600, 213), ((6, 128, 2048), 500, 0), ((6, 128, 2048), 8192, 256),
+    # more than 64 hidden units: rounds x outputs at and past the line
+    ((6, 128, 1024), 16384, 256), ((6, 128, 1025), 16384, 0), ((6, 128, 2048), 8193, 0),
+    ((6, 65, 256), 65536, 256), ((6, 65, 257), 65536, 0), ((6, 64, 4096), 1 << 20, 256),
+    # widths the kernel does not hold
+    ((33, 64, 20), 90, 0), ((6, 129, 20), 90, 0),
+])
+def test_networks_on_the_step_kernel(R, dims, rows, blocks):
+    assert R.step_blocks_c(*dims, rows, 256) == blocks
