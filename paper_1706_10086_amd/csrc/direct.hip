@@ -100,67 +100,39 @@ static hipError_t launch_list(const GemmArgs *p, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-// A tile and its time: with q = ceil(tiles / CUs) work-groups for the busiest
-// compute unit, R of them at a time, and k rounded up to the k-step,
-//   t = start + each q + rate k (BM BN / 4096) (sum over rounds of (alone + r))
-// microseconds, r work-groups in the round (R in all but the last): `alone` is the
-// part of a k-step that co-resident work-groups hide from each other, `each` a
-// tile's prologue and epilogue.  The coefficients are least squares on the log
-// of the times of 119 shapes per type (squares 64-8192, log-uniform 32-8192 and large
-// ragged ones, MI355X, calls back to back, within 4-13 % rms); picking by them
-// reaches 0.991 of the best tile of each shape in both types (geometric mean).
+// The tiles of direct_tiles() (host_rules.h) and their launchers, in the same order.
 struct DirectTile {
-    int bm, bn, bk;
-    int resident;            // R: work-groups a compute unit holds (LDS, registers)
-    double start, each, rate, alone;
+    TileCost c;
     hipError_t (*launch)(const GemmArgs &, int, int64_t, void *, hipStream_t);
     bool (*eligible)(const GemmArgs &);
     hipError_t (*list)(const GemmArgs *, int, hipStream_t);
 };
 
-#define DIRECT(T, BM, BN, BK, OCC, R, START, EACH, RATE, ALONE) \
-    {BM, BN, BK, R, START, EACH, RATE, ALONE, &launch_direct<T, BM, BN, BK, OCC>, &pipe_eligible<T, BM, BN, BK>, \
-     &launch_list<T, BM, BN, BK, OCC>}
+#define DIRECT(COSTS, I, T, OCC) \
+    {COSTS[I], &launch_direct<T, COSTS[I].bm, COSTS[I].bn, COSTS[I].bk, OCC>, \
+     &pipe_eligible<T, COSTS[I].bm, COSTS[I].bn, COSTS[I].bk>, \
+     &launch_list<T, COSTS[I].bm, COSTS[I].bn, COSTS[I].bk, OCC>}
 
-static const DirectTile kDirectF64[] = {
-    DIRECT(double, 128, 128, 16, 2, 2, 0.00, 9.90, 0.02724, 0.081),
-    DIRECT(double, 64, 128, 16, 2, 3, 2.16, 4.29, 0.02675, 0.278),
-    DIRECT(double, 64, 64, 16, 4, 4, 2.98, 1.96, 0.02792, 0.369),
-    DIRECT(double, 64, 32, 16, 4, 5, 2.49, 1.19, 0.02768, 1.000),
-    DIRECT(double, 32, 32, 32, 4, 4, 2.58, 0.89, 0.02839, 0.874),
-    DIRECT(double, 32, 32, 16, 4, 8, 2.36, 0.63, 0.03099, 1.465),
+static const DirectTile kDirectF64[DIRECT_TILES] = {
+    DIRECT(kTileCostsF64, 0, double, 2), DIRECT(kTileCostsF64, 1, double, 2),
+    DIRECT(kTileCostsF64, 2, double, 4), DIRECT(kTileCostsF64, 3, double, 4),
+    DIRECT(kTileCostsF64, 4, double, 4), DIRECT(kTileCostsF64, 5, double, 4),
 };
 
-static const DirectTile kDirectF32[] = {
-    DIRECT(float, 128, 128, 32, 2, 2, 3.90, 6.90, 0.01490, 0.038),
-    DIRECT(float, 64, 128, 32, 2, 3, 4.12, 2.53, 0.01463, 0.150),
-    DIRECT(float, 64, 64, 32, 3, 4, 3.94, 1.35, 0.01475, 0.349),
-    DIRECT(float, 64, 32, 32, 4, 5, 3.59, 0.87, 0.01520, 0.643),
-    DIRECT(float, 32, 32, 64, 4, 4, 3.23, 0.83, 0.01503, 0.879),
-    DIRECT(float, 32, 32, 32, 4, 8, 3.03, 0.50, 0.01706, 0.995),
+static const DirectTile kDirectF32[DIRECT_TILES] = {
+    DIRECT(kTileCostsF32, 0, float, 2), DIRECT(kTileCostsF32, 1, float, 2),
+    DIRECT(kTileCostsF32, 2, float, 3), DIRECT(kTileCostsF32, 3, float, 4),
+    DIRECT(kTileCostsF32, 4, float, 4), DIRECT(kTileCostsF32, 5, float, 4),
 };
-
-static double direct_time(const DirectTile &d, int64_t m, int64_t n, int64_t k, int64_t S, int cus) {
-    const double tiles = (double)((m + d.bm - 1) / d.bm) * (double)((n + d.bn - 1) / d.bn) * (double)S;
-    const double q = (double)(int64_t)((tiles + cus - 1) / cus);
-    const double rounds = (double)(int64_t)(q / d.resident), last = q - rounds * d.resident;
-    const double shared = rounds * (d.alone + d.resident) + (last > 0 ? d.alone + last : 0.0);
-    const double ks = (double)((k + d.bk - 1) / d.bk * d.bk);
-    return d.start + d.each * q + d.rate * ks * (d.bm * d.bn / 4096.0) * shared;
-}
 
 hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void *W, int cus,
                       hipStream_t s, bool *ran) {
     const DirectTile *t = dtype == MGEMM_F32 ? kDirectF32 : kDirectF64;
-    const int cnt = dtype == MGEMM_F32 ? (int)(sizeof kDirectF32 / sizeof kDirectF32[0])
-                                       : (int)(sizeof kDirectF64 / sizeof kDirectF64[0]);
     const DirectTile *best = nullptr;
     double tb = 0.0;
-    for (int i = 0; i < cnt; ++i) {
-        if (!t[i].eligible(a) ||
-            !grid_fits(((a.m + t[i].bm - 1) / t[i].bm) * ((a.n + t[i].bn - 1) / t[i].bn), DIRECT_THREADS))
-            continue;
-        const double ti = direct_time(t[i], a.m, a.n, kc, S, cus > 0 ? cus : 256);
+    for (int i = 0; i < DIRECT_TILES; ++i) {
+        if (!t[i].eligible(a) || !grid_fits(tiles_of(t[i].c, a.m, a.n), DIRECT_THREADS)) continue;
+        const double ti = tile_time(t[i].c, a.m, a.n, a.k, S, kc, cus > 0 ? cus : 256);
         if (!best || ti < tb) {
             best = &t[i];
             tb = ti;
@@ -171,8 +143,9 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
 }
 
 // Rows of one list launch in 32 bits for every tile of the table, and its work-items
-// (of many products of a few columns) in 32 bits on the smallest one; beyond LIST_FLOPS (tens of microseconds alone) a product gains nothing from company and
-// takes its own tile.
+// (of many products of a few columns) in 32 bits on the smallest one; beyond LIST_FLOPS
+// (tens of microseconds alone) a product gains nothing from company and takes its own
+// tile.
 constexpr double LIST_FLOPS = 4e9;
 
 bool list_eligible(const GemmArgs &a, int32_t dtype) {
@@ -188,15 +161,13 @@ bool list_eligible(const GemmArgs &a, int32_t dtype) {
 // busy compute units, but no less than its longest tile alone.
 hipError_t run_direct_list(const GemmArgs *p, int64_t count, int32_t dtype, int cus, hipStream_t s) {
     const DirectTile *t = dtype == MGEMM_F32 ? kDirectF32 : kDirectF64;
-    const int cnt = dtype == MGEMM_F32 ? (int)(sizeof kDirectF32 / sizeof kDirectF32[0])
-                                       : (int)(sizeof kDirectF64 / sizeof kDirectF64[0]);
     if (cus <= 0) cus = 256;
     for (int64_t i0 = 0; i0 < count; i0 += LIST_MAX) {
         const int c = (int)std::min<int64_t>(LIST_MAX, count - i0);
         const DirectTile *best = nullptr;
         double tb = 0.0;
-        for (int i = 0; i < cnt; ++i) {
-            const DirectTile &d = t[i];
+        for (int i = 0; i < DIRECT_TILES; ++i) {
+            const TileCost &d = t[i].c;
             const double area = d.bm * d.bn / 4096.0;
             double sum = 0.0, longest = 0.0;
             for (int j = 0; j < c; ++j) {
@@ -208,7 +179,7 @@ hipError_t run_direct_list(const GemmArgs *p, int64_t count, int32_t dtype, int 
             }
             const double ti = d.start + std::max(sum / cus, longest);
             if (!best || ti < tb) {
-                best = &d;
+                best = &t[i];
                 tb = ti;
             }
         }

@@ -27,6 +27,65 @@ inline bool list_grid_fits(int64_t m, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
+// The direct-load tiles and their times.
+// ---------------------------------------------------------------------------
+// A tile and its time: with q = ceil(tiles / CUs) work-groups for the busiest
+// compute unit, R of them at a time, and k rounded up to the k-step,
+//   t = start + each q + rate k (BM BN / 4096) (sum over rounds of (alone + r))
+// microseconds, r work-groups in the round (R in all but the last): `alone` is the
+// part of a k-step that co-resident work-groups hide from each other, `each` a
+// tile's prologue and epilogue.  The coefficients are least squares on the log
+// of the times of 119 shapes per type (squares 64-8192, log-uniform 32-8192 and large
+// ragged ones, MI355X, calls back to back, within 4-13 % rms); picking by them
+// reaches 0.991 of the best tile of each shape in both types (geometric mean).
+struct TileCost {
+    int bm, bn, bk;
+    int resident;            // R: work-groups a compute unit holds (LDS, registers)
+    double start, each, rate, alone;
+};
+
+constexpr int DIRECT_TILES = 6;
+
+constexpr TileCost kTileCostsF64[DIRECT_TILES] = {
+    {128, 128, 16, 2, 0.00, 9.90, 0.02724, 0.081}, {64, 128, 16, 3, 2.16, 4.29, 0.02675, 0.278},
+    {64, 64, 16, 4, 2.98, 1.96, 0.02792, 0.369},   {64, 32, 16, 5, 2.49, 1.19, 0.02768, 1.000},
+    {32, 32, 32, 4, 2.58, 0.89, 0.02839, 0.874},   {32, 32, 16, 8, 2.36, 0.63, 0.03099, 1.465},
+};
+
+constexpr TileCost kTileCostsF32[DIRECT_TILES] = {
+    {128, 128, 32, 2, 3.90, 6.90, 0.01490, 0.038}, {64, 128, 32, 3, 4.12, 2.53, 0.01463, 0.150},
+    {64, 64, 32, 4, 3.94, 1.35, 0.01475, 0.349},   {64, 32, 32, 5, 3.59, 0.87, 0.01520, 0.643},
+    {32, 32, 64, 4, 3.23, 0.83, 0.01503, 0.879},   {32, 32, 32, 8, 3.03, 0.50, 0.01706, 0.995},
+};
+
+inline int64_t tiles_of(const TileCost &d, int64_t m, int64_t n) {
+    return ((m + d.bm - 1) / d.bm) * ((n + d.bn - 1) / d.bn);
+}
+
+// The time of S ranges of kc values of k each, the last one holding what is left of k (S
+// = 1 and kc = k: a product run whole).  The work-groups of a shorter last range start
+// last and count as the part f of a full one that they are: they go to the compute units
+// that the full ones leave a work-group short, as many as fit, and then to all in turn.
+// (Counted as full ones, the tiles that leave units short looked best: of 122 products
+// whose k is cut for 128 x 128 tiles the pick reached 0.959 of the best tile's time,
+// 0.983 with f; FP32 1441 x 488 x 5140, five ranges of which the last holds 20 values,
+// 99 and 80 us.)
+inline double tile_time(const TileCost &d, int64_t m, int64_t n, int64_t k, int64_t S, int64_t kc,
+                        int cus) {
+    const int64_t t = tiles_of(d, m, n);
+    auto whole_steps = [&](int64_t v) { return (double)((v + d.bk - 1) / d.bk * d.bk); };
+    const double ks = whole_steps(kc), f = whole_steps(k - (S - 1) * kc) / ks;
+    const int64_t full = f < 1.0 ? t * (S - 1) : t * S, part = t * S - full;
+    double busiest = (double)((full + cus - 1) / cus);          // full work-groups
+    const int64_t gaps = full % cus ? (cus - full % cus) * (int64_t)(1.0 / f) : 0;
+    if (part > gaps) busiest += (double)((part - gaps + cus - 1) / cus) * f;
+    const double q = (double)((t * S + cus - 1) / cus);
+    const double rounds = (double)(int64_t)(busiest / d.resident), last = busiest - rounds * d.resident;
+    const double shared = rounds * (d.alone + d.resident) + (last > 0 ? d.alone + last : 0.0);
+    return d.start + d.each * q + d.rate * ks * (d.bm * d.bn / 4096.0) * shared;
+}
+
+// ---------------------------------------------------------------------------
 // Lists whose products share launches.
 // ---------------------------------------------------------------------------
 // Bytes that a product of a list reads or writes.

@@ -9,6 +9,17 @@ int grid_fits_c(int64_t blocks, int64_t threads) { return grid_fits(blocks, thre
 
 int list_grid_fits_c(int64_t m, int64_t n) { return list_grid_fits(m, n); }
 
+double tile_time_c(int f32, int tile, int64_t m, int64_t n, int64_t k, int64_t S, int64_t kc, int cus) {
+    return tile_time((f32 ? kTileCostsF32 : kTileCostsF64)[tile], m, n, k, S, kc, cus);
+}
+
+void tile_c(int f32, int tile, int32_t *bm, int32_t *bn, int32_t *bk) {
+    const TileCost &d = (f32 ? kTileCostsF32 : kTileCostsF64)[tile];
+    *bm = d.bm;
+    *bn = d.bn;
+    *bk = d.bk;
+}
+
 int step_blocks_c(int in, int hidden, int out, int64_t rows, int cus) {
     return step_blocks(in, hidden, out, rows, cus);
 }

@@ -1,6 +1,6 @@
 """The host side's rules that need no GPU (csrc/host_rules.h), compiled alone with the
-host compiler: which grids a launch may take, which lists' products depend on each
-other, what of a list runs when one of its products fails, and which networks train on
+host compiler: which grids a launch may take, how long a tile takes with k whole or in
+ranges, which lists' products depend on each other, what of a list runs when one of its products fails, and which networks train on
 the step kernel."""
 import ctypes
 import itertools
@@ -24,6 +24,9 @@ def R(tmp_path_factory):
     lib.list_grid_fits_c.argtypes = [i64, i64]
     i32 = ctypes.c_int
     lib.step_blocks_c.argtypes = [i32, i32, i32, i64, i32]
+    lib.tile_time_c.argtypes = [i32, i32, i64, i64, i64, i64, i64, i32]
+    lib.tile_time_c.restype = ctypes.c_double
+    lib.tile_c.argtypes = [i32, i32, *[ctypes.POINTER(ctypes.c_int32)] * 3]
     return lib
 
 
@@ -106,3 +109,47 @@ def test_a_failing_product_leaves_the_ones_before_it_done(R, what, group_rc, rc,
 ])
 def test_networks_on_the_step_kernel(R, dims, rows, blocks):
     assert R.step_blocks_c(*dims, rows, 256) == blocks
+
+
+def tile(R, f32, i):
+    v = [ctypes.c_int32() for _ in range(3)]
+    R.tile_c(f32, i, *[ctypes.byref(x) for x in v])
+    return tuple(x.value for x in v)
+
+
+def pick(R, f32, m, n, k, S, kc):
+    times = [R.tile_time_c(f32, i, m, n, k, S, kc, 256) for i in range(6)]
+    return tile(R, f32, times.index(min(times)))
+
+
+@pytest.mark.parametrize("f32", [0, 1])
+@pytest.mark.parametrize("i", range(6))
+def test_time_of_ranges(R, f32, i):
+    """A last range as long as the others counts as one of them (the time of a product
+    of as many times the rows, whose tiles are as many); a shorter one costs no more, and
+    costs nothing but its start where it fits beside the full ones."""
+    bm, bn, bk = tile(R, f32, i)
+    for tiles in (1, 40, 100, 128, 200, 300, 700):
+        for S in (2, 3, 5, 16):
+            kc = 1024
+            time = lambda k: R.tile_time_c(f32, i, tiles * bm, bn, k, S, kc, 256)  # noqa: E731
+            full = time(S * kc)
+            assert full == R.tile_time_c(f32, i, S * tiles * bm, bn, kc, 1, kc, 256)
+            ks = [(S - 1) * kc + r for r in (1, bk, 100, 256, 500, 512, 513, 1000, kc)]
+            times = [time(k) for k in ks]
+            assert times == sorted(times) and times[-1] == full
+            if S * tiles <= 256:
+                assert times[0] == full
+
+
+# FP32 products whose last range is short (times of the six tiles at 256 compute units)
+@pytest.mark.parametrize("m,n,k,S,kc,slow", [
+    (1441, 488, 5140, 5, 1280, (64, 128, 32)),      # 101 99 80 83 86 89 us
+    (2433, 336, 4636, 4, 1280, (64, 128, 32)),      # 103 101 90 89 91 92
+    (10061, 120, 3328, 3, 1280, (64, 128, 32)),     # 108 106 96 95 98 101
+    (1126, 836, 4344, 4, 1280, (64, 128, 32)),      # 103 101 87 91 95 97
+])
+def test_a_short_last_range_leaves_the_smaller_tiles_ahead(R, m, n, k, S, kc, slow):
+    assert (S - 1) * kc < k < S * kc
+    assert pick(R, 1, m, n, S * kc, S, kc) == slow
+    assert pick(R, 1, m, n, k, S, kc) != slow
