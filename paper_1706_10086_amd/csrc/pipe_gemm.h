@@ -55,7 +55,8 @@ inline bool pipe_eligible(const GemmArgs &a) {
 // last use, and k-step c+NST loads into the stage whose contents all waves already
 // hold in registers, so NST stages keep NST-1 k-steps in flight beside the one
 // being read.  One barrier per k-step.  The k-sum order per element is
-// gemm_tiled_kernel's, so both give bit-identical results.
+// gemm_tiled_kernel's, so both give bit-identical results (but for the sign of a sum
+// that underflows to zero: the zeros that pad k to a whole k-step make it positive).
 //
 // Rows and columns need no alignment beyond 4 bytes (16-byte loads at 4-byte
 // aligned addresses ran at the rate of aligned ones: 56-59 bytes per cycle and
@@ -220,7 +221,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
     // the loop; for the larger tiles (which have no registers to spare: FP64 128 x 128
     // x 16 spilled) it follows the loop.
     constexpr bool EARLY_TAIL = (NA + NB) * (int)sizeof(T) <= 64;
-    const int64_t steps = nk + (EARLY_TAIL && ktail ? 1 : 0);
+    // With k-steps of 32 and more, a product of less than one runs only the groups of 8
+    // that hold values (FP32 2047 x 12135 x 13: 41.5 us with all four groups and loads of
+    // clamped elements in place of the rows of B past k, 36.0 so; FP64's two groups of
+    // 64 x 64 x 16 have no registers left for the branch).
+    constexpr bool GROUPS = S::G > 2;
+    const int64_t steps = nk + (EARLY_TAIL && ktail && !(GROUPS && nk == 0) ? 1 : 0);
     T ta[NA], tb[NB];
     auto load_tail = [&]() {
         const AS_GLOBAL T *At = (const AS_GLOBAL T *)(Apanel + nk * (BK * (int64_t)sizeof(T)));
@@ -228,16 +234,14 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
 #pragma unroll
         for (int e = 0; e < NA; ++e) {
             const int r = (tid + e * S::NT) / BK, c = (tid + e * S::NT) % BK;
-            const bool in = r <= mlast && c < ktail;
-            ta[e] = At[(int64_t)(in ? r : 0) * lda + (in ? c : 0)];
-            if (!in) ta[e] = (T)0;
+            ta[e] = (T)0;
+            if (r <= mlast && c < ktail) ta[e] = At[(int64_t)r * lda + c];
         }
 #pragma unroll
         for (int e = 0; e < NB; ++e) {
             const int r = (tid + e * S::NT) / BN, c = (tid + e * S::NT) % BN;
-            const bool in = r < ktail && c < nlast;
-            tb[e] = Bt[(int64_t)(in ? r : 0) * ldb + (in ? c : 0)];
-            if (!in) tb[e] = (T)0;
+            tb[e] = (T)0;
+            if (r < ktail && c < nlast) tb[e] = Bt[(int64_t)r * ldb + c];
         }
     };
     auto store_tail = [&](u32x4_t *stage) {
@@ -261,7 +265,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
     if (nk >= NST) wait_steps(std::integral_constant<int, NST - 1>());
     else wait_steps(std::integral_constant<int, 0>());
     __syncthreads();
-    if (live) {
+    if (live && (!GROUPS || nk > 0)) {
 #pragma unroll
         for (int g = 0; g < S::G; ++g) {
 #pragma unroll
@@ -296,14 +300,17 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
             products(std::false_type(), std::true_type(), lds + st1 * S::STAGE, 0, lds);
         st = st1;
     }
-    if (!EARLY_TAIL && ktail) {
-        load_tail();
-        __syncthreads();                 // every wave is done with LDS
-        store_tail(lds);
-        __syncthreads();
+    if (EARLY_TAIL ? GROUPS && nk == 0 : ktail != 0) {
+        if (!EARLY_TAIL) {
+            load_tail();
+            __syncthreads();             // every wave is done with LDS
+            store_tail(lds);
+            __syncthreads();
+        }
         if (live) {
 #pragma unroll
             for (int g = 0; g < S::G; ++g) {
+                if (GROUPS && g * 8 >= ktail) break;
 #pragma unroll
                 for (int i = 0; i < S::FM; ++i) read_a(lds, g, i);
                 read_b(lds, g, 0);
@@ -316,6 +323,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs &p, u32x4_t *lds, int64
                         for (int j = 0; j < S::FN; ++j)
                             acc[i][j] = E::mma(af[g][i][h], bf[g][h][j], acc[i][j]);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            // what the products of the groups left out would add
+            if (GROUPS && ktail <= BK - 8) {
+#pragma unroll
+                for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < S::FN; ++j) acc[i][j] += acc4{0, 0, 0, 0};
             }
         }
     }
