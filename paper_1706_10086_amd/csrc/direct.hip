@@ -130,9 +130,12 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
     const DirectTile *t = dtype == MGEMM_F32 ? kDirectF32 : kDirectF64;
     const DirectTile *best = nullptr;
     double tb = 0.0;
+    if (cus <= 0) cus = 256;
     for (int i = 0; i < DIRECT_TILES; ++i) {
-        if (!t[i].eligible(a) || !grid_fits(tiles_of(t[i].c, a.m, a.n), DIRECT_THREADS)) continue;
-        const double ti = tile_time(t[i].c, a.m, a.n, a.k, S, kc, cus > 0 ? cus : 256);
+        if (!t[i].eligible(a) || !grid_fits(tiles_of(t[i].c, a.m, a.n), DIRECT_THREADS) ||
+            !tile_taken(t[i].c, a.m, a.n, a.k, S, cus))
+            continue;
+        const double ti = tile_time(t[i].c, a.m, a.n, a.k, S, kc, cus);
         if (!best || ti < tb) {
             best = &t[i];
             tb = ti;

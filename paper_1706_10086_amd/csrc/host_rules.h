@@ -85,6 +85,17 @@ inline double tile_time(const TileCost &d, int64_t m, int64_t n, int64_t k, int6
     return d.start + d.each * q + d.rate * ks * (d.bm * d.bn / 4096.0) * shared;
 }
 
+// Whether a product may run on the tile.  The coefficients, fitted to longer products,
+// make the 128-wide tiles of a short product look better than they are where all of its
+// 64 x 64 tiles are resident at once: of 16 such products with k up to 512 that the
+// estimate gave to a 128-wide tile none ran faster there (1.03-1.37x as fast on the best
+// of the others: FP64 722 x 4414 x 32 13.7 and 11.6 us, FP32 1330 x 1468 x 27 11.2 and
+// 8.6).  With k = 2048 the 128-wide tiles win (FP32 2048 x 2048: 133 and 138).
+inline bool tile_taken(const TileCost &d, int64_t m, int64_t n, int64_t k, int64_t S, int cus) {
+    const TileCost square = {64, 64, 0, 4, 0, 0, 0, 0};
+    return !(S == 1 && k <= 512 && d.bn >= 128 && tiles_of(square, m, n) <= (int64_t)square.resident * cus);
+}
+
 // ---------------------------------------------------------------------------
 // Lists whose products share launches.
 // ---------------------------------------------------------------------------

@@ -13,6 +13,10 @@ double tile_time_c(int f32, int tile, int64_t m, int64_t n, int64_t k, int64_t S
     return tile_time((f32 ? kTileCostsF32 : kTileCostsF64)[tile], m, n, k, S, kc, cus);
 }
 
+int tile_taken_c(int f32, int tile, int64_t m, int64_t n, int64_t k, int64_t S, int cus) {
+    return tile_taken((f32 ? kTileCostsF32 : kTileCostsF64)[tile], m, n, k, S, cus);
+}
+
 void tile_c(int f32, int tile, int32_t *bm, int32_t *bn, int32_t *bk) {
     const TileCost &d = (f32 ? kTileCostsF32 : kTileCostsF64)[tile];
     *bm = d.bm;

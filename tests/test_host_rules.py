@@ -26,6 +26,7 @@ def R(tmp_path_factory):
     lib.step_blocks_c.argtypes = [i32, i32, i32, i64, i32]
     lib.tile_time_c.argtypes = [i32, i32, i64, i64, i64, i64, i64, i32]
     lib.tile_time_c.restype = ctypes.c_double
+    lib.tile_taken_c.argtypes = [i32, i32, i64, i64, i64, i64, i32]
     lib.tile_c.argtypes = [i32, i32, *[ctypes.POINTER(ctypes.c_int32)] * 3]
     return lib
 
@@ -118,8 +119,9 @@ def tile(R, f32, i):
 
 
 def pick(R, f32, m, n, k, S, kc):
-    times = [R.tile_time_c(f32, i, m, n, k, S, kc, 256) for i in range(6)]
-    return tile(R, f32, times.index(min(times)))
+    times = {i: R.tile_time_c(f32, i, m, n, k, S, kc, 256) for i in range(6)
+             if R.tile_taken_c(f32, i, m, n, k, S, 256)}
+    return tile(R, f32, min(times, key=times.get))
 
 
 @pytest.mark.parametrize("f32", [0, 1])
@@ -153,3 +155,25 @@ def test_a_short_last_range_leaves_the_smaller_tiles_ahead(R, m, n, k, S, kc, sl
     assert (S - 1) * kc < k < S * kc
     assert pick(R, 1, m, n, S * kc, S, kc) == slow
     assert pick(R, 1, m, n, k, S, kc) != slow
+
+
+@pytest.mark.parametrize("f32,m,n,k", [(0, 722, 4414, 32), (0, 7462, 446, 2), (0, 834, 2120, 109),
+                                       (0, 1038, 3158, 95), (1, 247, 12851, 45), (1, 1330, 1468, 27)])
+def test_short_products_of_one_round_leave_the_wide_tiles(R, f32, m, n, k):
+    """Products that the wide tiles' estimates undercut, each 4-20 % slower there."""
+    times = [R.tile_time_c(f32, i, m, n, k, 1, k, 256) for i in range(6)]
+    assert tile(R, f32, times.index(min(times)))[1] == 128
+    assert pick(R, f32, m, n, k, 1, k)[1] < 128
+
+
+def test_where_the_wide_tiles_are_left_out(R):
+    """Whole products of at most 512 k whose 64 x 64 tiles are resident at once (four to a
+    compute unit); ranges of k, longer and larger products keep every tile."""
+    for f32 in (0, 1):
+        for i in range(6):
+            wide = tile(R, f32, i)[1] == 128
+            taken = lambda *a: bool(R.tile_taken_c(f32, i, *a, 256))  # noqa: E731
+            assert taken(2048, 2048, 512, 1) == (not wide)
+            assert taken(1, 1, 1, 1) == (not wide)
+            assert taken(2048, 2048, 513, 1) and taken(2048, 2049, 512, 1)
+            assert taken(2049, 2048, 512, 1) and taken(256, 256, 4096, 8)
