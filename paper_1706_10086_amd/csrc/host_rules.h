@@ -26,6 +26,10 @@ inline bool list_grid_fits(int64_t m, int64_t n) {
     return grid_fits(tiles * LIST_MAX, DIRECT_THREADS);
 }
 
+// Whether a buffer of `have` bytes holds `need`, or one of `need` bytes fits the free
+// memory once it is given back.
+inline bool may_hold(size_t have, size_t free, size_t need) { return have >= need || have + free >= need; }
+
 // ---------------------------------------------------------------------------
 // The direct-load tiles and their times.
 // ---------------------------------------------------------------------------

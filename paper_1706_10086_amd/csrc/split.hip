@@ -1048,6 +1048,16 @@ static int32_t ws_reserve(Workspace &w, size_t bytes) {
     return 0;
 }
 
+// Whether the workspace holds `bytes` or may be grown to them.
+static bool ws_may_hold(const Workspace &w, size_t bytes) {
+    size_t free = 0, all = 0;
+    if (w.bytes < bytes && hipMemGetInfo(&free, &all) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return may_hold(w.bytes, free, bytes);
+}
+
 // The row and column exponents of g's operands on s, into e and fexp (np entries);
 // scale_check then waits for them (and not for what was queued after them) and reports
 // non-finite input.
@@ -1169,9 +1179,13 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
             part_bytes = bytes > part_bytes ? bytes : part_bytes;
         }
     const size_t total = e_bytes + f_bytes + a_bytes + b_bytes + s_bytes;
-    int32_t rc = ws_reserve(w, total + part_bytes);
+    // no room for the ranges' sums: every tile whole.  The free memory is asked for first,
+    // so that a workspace that holds the rest is not given up for one that cannot be had
+    // (each call would free and allocate it again)
+    int32_t rc = part_bytes && !ws_may_hold(w, total + part_bytes) ? MGEMM_ERR_NOMEM
+                                                                   : ws_reserve(w, total + part_bytes);
     if (rc == MGEMM_ERR_NOMEM && part_bytes) {
-        // no room for the ranges' sums: every tile whole
+        set_error(0, "%s", "");
         plans[0] = plans[1] = PairPlan{blocks, 1, kch};
         part_bytes = 0;
         rc = ws_reserve(w, total);

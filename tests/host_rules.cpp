@@ -7,6 +7,8 @@ extern "C" {
 
 int grid_fits_c(int64_t blocks, int64_t threads) { return grid_fits(blocks, threads); }
 
+int may_hold_c(int64_t have, int64_t free, int64_t need) { return may_hold(have, free, need); }
+
 int list_grid_fits_c(int64_t m, int64_t n) { return list_grid_fits(m, n); }
 
 double tile_time_c(int f32, int tile, int64_t m, int64_t n, int64_t k, int64_t S, int64_t kc, int cus) {

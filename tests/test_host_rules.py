@@ -22,6 +22,7 @@ def R(tmp_path_factory):
     i64 = ctypes.c_int64
     lib.grid_fits_c.argtypes = [i64, i64]
     lib.list_grid_fits_c.argtypes = [i64, i64]
+    lib.may_hold_c.argtypes = [i64, i64, i64]
     i32 = ctypes.c_int
     lib.step_blocks_c.argtypes = [i32, i32, i32, i64, i32]
     lib.tile_time_c.argtypes = [i32, i32, i64, i64, i64, i64, i64, i32]
@@ -177,3 +178,10 @@ def test_where_the_wide_tiles_are_left_out(R):
             assert taken(1, 1, 1, 1) == (not wide)
             assert taken(2048, 2048, 513, 1) and taken(2048, 2049, 512, 1)
             assert taken(2049, 2048, 512, 1) and taken(256, 256, 4096, 8)
+
+
+def test_a_workspace_is_given_up_only_for_one_that_fits(R):
+    """100 bytes held, 120 wanted: grown with 20 free, kept with 19; what is held needs
+    no free memory."""
+    assert R.may_hold_c(100, 20, 120) and not R.may_hold_c(100, 19, 120)
+    assert R.may_hold_c(120, 0, 120) and R.may_hold_c(0, 120, 120) and not R.may_hold_c(0, 119, 120)
