@@ -1055,7 +1055,8 @@ static bool ws_may_hold(const Workspace &w, size_t bytes) {
         (void)hipGetLastError();
         return true;
     }
-    return may_hold(w.bytes, free, bytes);
+    // (the runtime's count of free bytes has passed below zero here, on a full device)
+    return may_hold(w.bytes, free <= all ? free : 0, bytes);
 }
 
 // The row and column exponents of g's operands on s, into e and fexp (np entries);
