@@ -145,18 +145,8 @@ hipError_t run_direct(const GemmArgs &a, int32_t dtype, int S, int64_t kc, void 
     return best ? best->launch(a, S, kc, W, s) : hipSuccess;
 }
 
-// Rows of one list launch in 32 bits for every tile of the table, and its work-items
-// (of many products of a few columns) in 32 bits on the smallest one; beyond LIST_FLOPS
-// (tens of microseconds alone) a product gains nothing from company and takes its own
-// tile.
-constexpr double LIST_FLOPS = 4e9;
-
 bool list_eligible(const GemmArgs &a, int32_t dtype) {
-    const int64_t es = (int64_t)elem_size(dtype), lim = (int64_t)1 << 31;
-    return a.m >= 1 && a.k >= 1 && a.n >= 16 / es && ((uintptr_t)a.A % 4) == 0 &&
-           ((uintptr_t)a.B % 4) == 0 && a.m < lim && a.k < lim && 128 * a.lda * es < lim &&
-           (64 * a.ldb + 128) * es < lim && a.ldc < lim && list_grid_fits(a.m, a.n) &&
-           2.0 * (double)a.m * (double)a.n * (double)a.k <= LIST_FLOPS;
+    return list_joins((int64_t)elem_size(dtype), a.m, a.n, a.k, a.A, a.lda, a.B, a.ldb, a.ldc);
 }
 
 // The products (list_eligible, any order) in launches of up to LIST_MAX, longest k

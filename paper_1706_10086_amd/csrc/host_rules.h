@@ -16,14 +16,37 @@ inline bool grid_fits(int64_t blocks, int64_t threads) { return blocks <= 0xFFFF
 
 // Work-groups of the direct-load kernels that share launches or a plan.
 constexpr int64_t DIRECT_THREADS = 256;
+
+// Whether the direct-load tiles of BM x BN x BK take a product's operands (es: bytes of an
+// element): at least one 16-byte unit per row of A and B, bases on 4-byte boundaries
+// (the direct loads take any such address) and panels that 32-bit byte offsets span.
+inline bool direct_loads(int64_t es, int64_t bm, int64_t bn, int64_t bk, int64_t m, int64_t n, int64_t k,
+                         const void *A, int64_t lda, const void *B, int64_t ldb) {
+    const int64_t lim = (int64_t)1 << 31;
+    return m >= 1 && k >= 1 && n >= 16 / es && ((uintptr_t)A % 4) == 0 && ((uintptr_t)B % 4) == 0 &&
+           bm * lda * es < lim && (bk * ldb + bn) * es < lim;
+}
+
 // Products of one shared launch at most (their descriptions stay below 4 KiB of kernel
 // arguments).
 constexpr int LIST_MAX = 56;
+// Beyond this (tens of microseconds alone) a product gains nothing from company and takes
+// its own tile.
+constexpr double LIST_FLOPS = 4e9;
 
 // Whether LIST_MAX products of m x n may share a launch on the smallest tile.
 inline bool list_grid_fits(int64_t m, int64_t n) {
     const int64_t tiles = ((m + 31) / 32) * ((n + 31) / 32);
     return grid_fits(tiles * LIST_MAX, DIRECT_THREADS);
+}
+
+// Whether a product may share a launch: operands, rows and work-items in 32 bits on every
+// tile of the table.
+inline bool list_joins(int64_t es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
+                       const void *B, int64_t ldb, int64_t ldc) {
+    const int64_t lim = (int64_t)1 << 31;
+    return direct_loads(es, 128, 128, 64, m, n, k, A, lda, B, ldb) && m < lim && k < lim && ldc < lim &&
+           2.0 * (double)m * (double)n * (double)k <= LIST_FLOPS && list_grid_fits(m, n);
 }
 
 // Whether a buffer of `have` bytes holds `need`, or one of `need` bytes fits the free

@@ -35,15 +35,10 @@ struct PipeShape {
     static constexpr int LOADS = (STAGE + NT - 1) / NT;            // load instructions per wave
 };
 
-// Whether pipe_tile can run a product with tiles of BM x BN x BK: at least one
-// 16-byte unit per row of A and B, bases on 4-byte boundaries (the direct loads
-// take any such address) and panels that 32-bit byte offsets span.
+// Whether pipe_tile can run a product with tiles of BM x BN x BK.
 template <typename T, int BM, int BN, int BK>
 inline bool pipe_eligible(const GemmArgs &a) {
-    constexpr int64_t EPU = 16 / (int64_t)sizeof(T), ES = sizeof(T);
-    return a.m >= 1 && a.k >= 1 && a.n >= EPU && ((uintptr_t)a.A % 4) == 0 &&
-           ((uintptr_t)a.B % 4) == 0 && BM * a.lda * ES < ((int64_t)1 << 31) &&
-           (BK * a.ldb + BN) * ES < ((int64_t)1 << 31);
+    return direct_loads(sizeof(T), BM, BN, BK, a.m, a.n, a.k, a.A, a.lda, a.B, a.ldb);
 }
 
 // One BM x BN tile of C: rows from m0, columns [c0, c0 + BN) of which this tile

@@ -9,6 +9,16 @@ int grid_fits_c(int64_t blocks, int64_t threads) { return grid_fits(blocks, thre
 
 int may_hold_c(int64_t have, int64_t free, int64_t need) { return may_hold(have, free, need); }
 
+int direct_loads_c(int64_t es, int64_t bm, int64_t bn, int64_t bk, int64_t m, int64_t n, int64_t k,
+                   int64_t A, int64_t lda, int64_t B, int64_t ldb) {
+    return direct_loads(es, bm, bn, bk, m, n, k, (const void *)A, lda, (const void *)B, ldb);
+}
+
+int list_joins_c(int64_t es, int64_t m, int64_t n, int64_t k, int64_t A, int64_t lda, int64_t B,
+                 int64_t ldb, int64_t ldc) {
+    return list_joins(es, m, n, k, (const void *)A, lda, (const void *)B, ldb, ldc);
+}
+
 int list_grid_fits_c(int64_t m, int64_t n) { return list_grid_fits(m, n); }
 
 double tile_time_c(int f32, int tile, int64_t m, int64_t n, int64_t k, int64_t S, int64_t kc, int cus) {

@@ -1,5 +1,5 @@
 """The host side's rules that need no GPU (csrc/host_rules.h), compiled alone with the
-host compiler: which grids a launch may take, how long a tile takes with k whole or in
+host compiler: which operands the direct loads take and which grids a launch, how long a tile takes with k whole or in
 ranges, which lists' products depend on each other, what of a list runs when one of its products fails, and which networks train on
 the step kernel."""
 import ctypes
@@ -7,6 +7,7 @@ import itertools
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -23,6 +24,8 @@ def R(tmp_path_factory):
     lib.grid_fits_c.argtypes = [i64, i64]
     lib.list_grid_fits_c.argtypes = [i64, i64]
     lib.may_hold_c.argtypes = [i64, i64, i64]
+    lib.direct_loads_c.argtypes = [i64] * 11
+    lib.list_joins_c.argtypes = [i64] * 9
     i32 = ctypes.c_int
     lib.step_blocks_c.argtypes = [i32, i32, i32, i64, i32]
     lib.tile_time_c.argtypes = [i32, i32, i64, i64, i64, i64, i64, i32]
@@ -185,3 +188,48 @@ def test_a_workspace_is_given_up_only_for_one_that_fits(R):
     no free memory."""
     assert R.may_hold_c(100, 20, 120) and not R.may_hold_c(100, 19, 120)
     assert R.may_hold_c(120, 0, 120) and R.may_hold_c(0, 120, 120) and not R.may_hold_c(0, 119, 120)
+
+
+BASE = 1 << 20
+
+
+@pytest.mark.parametrize("es", [8, 4])
+def test_what_the_direct_loads_take(R, es):
+    loads = lambda m=64, n=64, k=64, A=BASE, lda=64, B=BASE, ldb=64: bool(  # noqa: E731
+        R.direct_loads_c(es, 128, 128, 32, m, n, k, A, lda, B, ldb))
+    assert loads() and loads(1, 16 // es, 1)
+    assert not loads(n=16 // es - 1) and not loads(m=0) and not loads(k=0)
+    assert loads(A=BASE + 4) and loads(B=BASE + 12)
+    assert not loads(A=BASE + 2) and not loads(B=BASE + 1)
+    # 128 rows of A, 32 of B and a row's 128 elements below 2^31 bytes
+    edge = (1 << 31) // (128 * es)
+    assert loads(lda=edge - 1) and not loads(lda=edge)
+    edge = ((1 << 31) // es - 128) // 32
+    assert loads(ldb=edge - 1) and not loads(ldb=edge)
+
+
+@pytest.mark.parametrize("es", [8, 4])
+def test_plans_and_lists_under_gpu_test_take_both_paths(R, es):
+    """The shapes of the GPU tests that compare a default plan and a list with products in
+    turn: some of them are for the direct loads and some are not, and the list has more
+    products that share launches than one launch takes."""
+    off = 4 if es == 4 else 8
+    plan = [(1, 1, 1), (70, 1, 33), (65, 2, 64), (20, 3, 17), (129, 5, 40), (64, 64, 48), (63, 65, 1),
+            (200, 333, 77), (333, 200, 130), (17, 1000, 5), (1000, 17, 250)]
+    direct = [bool(R.direct_loads_c(es, 64, 64, 32 if es == 4 else 16, m, n, k, BASE + off * (n % 2),
+                                    k + (m + n) % 3, BASE + off * (m % 4), n + k % 2))
+              for m, n, k in plan]
+    assert direct == [n >= 16 // es for _, n, _ in plan] and set(direct) == {True, False}
+    rng = np.random.RandomState(5)
+    shapes = [tuple(int(2.0 ** rng.uniform(0, 8)) for _ in range(3)) for _ in range(130)]
+    shapes += [(700, 650, 600), (33, 2, 9), (40, 1, 40), (1, 1, 1)]
+    joins = [bool(R.list_joins_c(es, m, n, k, BASE + off, k + 2, BASE + off, n + 1, n + 4))
+             for m, n, k in shapes]
+    assert sum(joins) > 56 and not all(joins)
+
+
+def test_which_products_share_launches(R):
+    joins = lambda m, n, k, ld=0: bool(R.list_joins_c(8, m, n, k, BASE, max(k, ld), BASE, n, n))  # noqa: E731
+    assert joins(1000, 1000, 2000) and not joins(1000, 1000, 2001)        # 4e9 operations
+    assert joins(100, 100, 100, (1 << 21) - 1) and not joins(100, 100, 100, 1 << 21)
+    assert not joins(100, 1, 100) and not joins(1 << 27, 2, 1)
