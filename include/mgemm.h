@@ -113,7 +113,7 @@ MGEMM_API int32_t gemm(int64_t m, int64_t n, int64_t k, double alpha,
  * 2048 or m, n or k lies outside [64, 16384]; otherwise, with a cost model loaded
  * (mgemm_model_load) and m, n, k in [64, 16384], its prediction; else, for rows
  * of whole 16-byte loads (n, lda, ldb multiples of 16 bytes, A and B
- * 16-byte aligned), the direct-load tile (256 x 128, 128 x 128 or 64 x 64) whose
+ * 16-byte aligned), the tile (256 x 128, 128 x 128 or 64 x 64) whose
  * sustained rate times the fill of its rounds of one work-group per compute unit
  * is highest, if that fill is at least 80 % -- or, where 128 x 128 tiles leave a
  * last round of few tiles, the tile rows that fill whole rounds whole and the
@@ -128,7 +128,8 @@ MGEMM_API int32_t gemm(int64_t m, int64_t n, int64_t k, double alpha,
  * of k: the whole products and k ranges of the built-in choice (no cfg, no model)
  * are executed by the direct-load tile estimated fastest for their shape, rows of
  * any alignment, with the bits of the configuration chosen; the chosen one itself
- * runs where the direct loads cannot (see double_buffer).
+ * runs where the direct loads cannot (see double_buffer), and where A or B of a
+ * large product run whole lies in host memory.
  *
  * Split-k (MGEMM_F64 and MGEMM_F32, cfg == NULL only, k >= 2048 or outside the
  * measured range): when the preferred tile leaves fewer than about four
@@ -315,7 +316,12 @@ MGEMM_API int32_t mlp_save(void *mlp, const char *path, const int32_t *out_dtype
  * a model loaded, gemm_ex with cfg == NULL (MGEMM_F64, MGEMM_F32) runs the
  * model's prediction for shapes with m, n, k in [64, 16384] (the range it
  * learned) instead of the built-in table, except where the built-in choice cuts
- * k (split-k: no model output stands for it).  The
+ * k (split-k: no model output stands for it).  The prediction is a registered
+ * configuration and runs as it is.  Without a model the built-in choice runs on
+ * direct-load tiles that no registered configuration names and is faster on most
+ * shapes now (on 8 held-out FP64 shapes 1.22 of the best registered configuration,
+ * MI355X), and a product with a predicted configuration shares no launch in
+ * gemm_batched: load a model to have its configurations run, not for speed.  The
  * first such call for a shape evaluates the network on the current device with
  * the library's kernels and waits for it (calls on a stream being captured into a
  * graph use a prediction only if one is already cached);

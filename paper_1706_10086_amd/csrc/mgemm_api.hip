@@ -268,6 +268,12 @@ bool capturing(hipStream_t s) {
 // three quarters of the compute units in one round, else, for FP64 only, the chosen
 // two-stage tile about four work-groups per compute unit (for FP32, twice as
 // fast per tile, that lost 4 % to the extra reduction, so FP32 then runs whole).
+// These lines were drawn with the three-stage and register-staged kernels that ran the
+// ranges then; the ranges run on any direct-load tile and any rows now, and the lines
+// stay because they fix the order of the sums.  What they cost: FP32 300 x 129 x 10007
+// (not whole 16-byte rows) runs whole in 90 us where FP64 takes 35 in 14 ranges, and 512
+// x 511 x 16384 in 149 where 512 x 512 x 16384 takes 77 in 16 (before the direct-load
+// tiles 175, 65, 292 and 81).
 constexpr int64_t SPLITK_MIN_K = 256;
 constexpr int64_t SPLITK_FIRST_K = 2048;
 constexpr int SPLITK_MAX = 16;
@@ -328,8 +334,35 @@ int32_t launch_splitk_into(const KernelEntry *e, const GemmArgs &a, int32_t dtyp
     return he == hipSuccess ? 0 : hip_error(he, "split-k launch");
 }
 
+// Whether p lies in host memory (mapped or managed); unknown addresses count as device
+// memory.
+static bool in_host_memory(const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeHost || at.type == hipMemoryTypeManaged;
+}
+
+// A large product whose A or B lies in host memory runs on the plan's own configuration.
+// Over the host link the bytes that an L2 loses and asks for again decide, and the
+// direct-load tiles' work-groups, several to a compute unit, drift further apart in k than
+// one large tile per compute unit does: FP64 8192^3 924 ms on the direct-load tile and
+// 285-420 on the 256 x 128 configuration, FP32 8192^3 384 and 127, 1024 x 16384 x 8192 52
+// and 22.  (The 64 x 64 x 32 configuration, which shares compute units since it has two
+// stages, keeps part of the loss: FP32 3072^3 11.5 ms, 9.7 with three.)  Below
+// HOST_CHECK_FLOPS (130 us in FP32 from device memory, beside which asking for two
+// pointers' memory is nothing) neither is slower by more than 4 %.
+constexpr double HOST_CHECK_FLOPS = 2e10;
+
+static bool large_from_host(const GemmArgs &a) {
+    return 2.0 * (double)a.m * (double)a.n * (double)a.k >= HOST_CHECK_FLOPS &&
+           (in_host_memory(a.A) || in_host_memory(a.B));
+}
+
 hipError_t launch_whole(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s) {
-    if (!cp.named) {
+    if (!cp.named && !large_from_host(a)) {
         bool ran = false;
         const hipError_t he = run_direct(a, dtype, 1, a.k, nullptr, compute_units(), s, &ran);
         if (he != hipSuccess || ran) return he;
@@ -346,16 +379,17 @@ static int32_t run_splitk(const KernelEntry *e, const GemmArgs &a, int32_t dtype
     });
 }
 
-// Direct-load tiles for rows that are whole 16-byte loads, each with the rate it
-// sustains while every compute unit is busy (TFLOP/s: square N = 12288 on MI355X,
-// calls back to back).  A product of T tiles of one of them runs in
-// R = ceil(T / CUs) rounds that are T / (R CUs) full; the built-in choice takes
-// the tile with the highest rate times fill when that fill is at least
+// Tiles for rows that are whole 16-byte loads, each with the rate that its three-stage
+// kernel sustained while every compute unit was busy (TFLOP/s: square N = 12288 on
+// MI355X, calls back to back; these configurations, named, reach 73.8, 71.6 and 67.7 in
+// FP64 and 143.7, 137.3 and 136.3 in FP32 with two stages).  A product of T tiles of one
+// of them runs in R = ceil(T / CUs) rounds that are T / (R CUs) full; the built-in choice
+// reports the tile with the highest rate times fill when that fill is at least
 // WAVE_FILL_MIN (fewer tiles than that: the measured table decides).  On the
 // tuner's shapes with such rows this came 1.1 % (FP64) and 1.4-2.3 % (FP32) closer
-// to the exhaustive best than the preference list and table alone; at N = 6144 FP64
-// it takes the 128 x 128 tile (2304 tiles, 9 full rounds: 70 TFLOP/s) over the
-// 256 x 128 one (1152 tiles, 4.5 rounds: 65).
+// to the exhaustive best of those kernels than the preference list and table alone.  The
+// reported tile only names the sums' order (the direct-load tile estimated fastest runs);
+// the rates still decide the split tail below.
 struct PipeRate {
     mgemm_cfg cfg;
     double tflops;
@@ -406,10 +440,14 @@ static const KernelEntry *wave_filled_pipe(const GemmArgs &a, int32_t dtype, dou
 // TAIL_RATE_FACTOR of that rate x its fill (shorter k-loops), the sum at
 // SUM_BYTES_PER_S -- beats plain_tf, the best single-tile estimate, by TAIL_GAIN,
 // or by TAIL_GAIN_LARGE where that tile is a 128 x 128 or 256 x 128 one.
-// (N = 3072 FP64: 21 of 24 tile rows whole in two full rounds, 3 rows in 3 ranges
-// of 1024: 53 -> 65 TFLOP/s.  On the tuner's shapes whose estimate beat the best
-// single tile by 2-5 %, the tail measured 1.003-1.073x as fast where that tile was
-// 128 x 128 or 256 x 128, but 0.93-1.07x where it was 64 x 64.)
+// (N = 3072: 21 of 24 tile rows whole in two full rounds, 3 rows in 3 ranges of 1024.)
+// The bars were set on the three-stage kernels: on the tuner's shapes whose estimate beat
+// the best single tile by 2-5 %, the tail measured 1.003-1.073x as fast where that tile
+// was 128 x 128 or 256 x 128, but 0.93-1.07x where it was 64 x 64.  Against the direct-load
+// tile that would run the product whole, both parts on direct-load tiles, the tail
+// is 1.02-1.06x as fast in FP64 (N = 3584 1339 against 1400 us, 4608 2776 and 2939, 5120
+// 3756 and 3828, 7168 10225 and 10423, 7680 12465 and 13169, 8704 18133 and 18799, 9216
+// 21332 and 22027; but 3072 854 and 835) and 1.02-1.07x in FP32 (3072: the same).
 constexpr double TAIL_RATE_FACTOR = 0.8;
 constexpr double SUM_BYTES_PER_S = 4e12;
 constexpr double TAIL_GAIN = 1.05;
@@ -486,8 +524,8 @@ int32_t plan_call(const GemmArgs &a, int32_t dtype, const mgemm_cfg *cfg,
             }
         }
         // rows of whole 16-byte loads: a split tail where it pays, else the
-        // direct-load tile that fills the compute units' rounds best, where one
-        // fills them well enough
+        // tile that fills the compute units' rounds best, where one fills them
+        // well enough
         if (rows16) {
             double best_tf = 0.0;
             bool best_large = false;
