@@ -310,7 +310,7 @@ hipError_t launch_pipe(const GemmArgs &a, hipStream_t s) {
 }
 
 // Registry entry of a direct-load configuration (double_buffer = 2); batched plans
-// use the two-stage kernel of the same tile.
+// and large products from host memory use the two-stage kernel of the same tile.
 // Its elems_per_thread is the elements of one 16-byte direct load; FWGM, FWGN and
 // FEPT name the two-stage fallback (registered on its own as well).
 #define MGEMM_PIPE_CFG(T, BM, BN, BK, WGM, WGN, FWGM, FWGN, FEPT)                      \
@@ -318,7 +318,10 @@ hipError_t launch_pipe(const GemmArgs &a, hipStream_t s) {
      &launch_pipe<T, BM, BN, BK, WGM, WGN, FWGM, FWGN, FEPT, true>,                       \
      &launch_pipe<T, BM, BN, BK, WGM, WGN, FWGM, FWGN, FEPT, false>,                      \
      &launch_batched<T, BM, BN, BK, FWGM, FWGN, FEPT, 1, 0>,                               \
-     &batched_occupancy<T, BM, BN, BK, FWGM, FWGN, FEPT, 1, 0>}
+     &batched_occupancy<T, BM, BN, BK, FWGM, FWGN, FEPT, 1, 0>,                            \
+     {nullptr, nullptr},                                                                  \
+     {&launch_tiled<T, BM, BN, BK, FWGM, FWGN, FEPT, 1, 0, true>,                         \
+      &launch_tiled<T, BM, BN, BK, FWGM, FWGN, FEPT, 1, 0, false>}}
 
 // A two-stage configuration that also runs split-k for the built-in choice (FP64
 // only: at N = 1024 it raised FP64 from 27.0 to 30.9 TFLOP/s, while FP32, twice as

@@ -345,15 +345,16 @@ static bool in_host_memory(const void *p) {
     return at.type == hipMemoryTypeHost || at.type == hipMemoryTypeManaged;
 }
 
-// A large product whose A or B lies in host memory runs on the plan's own configuration.
-// Over the host link the bytes that an L2 loses and asks for again decide, and the
-// direct-load tiles' work-groups, several to a compute unit, drift further apart in k than
-// one large tile per compute unit does: FP64 8192^3 924 ms on the direct-load tile and
-// 285-420 on the 256 x 128 configuration, FP32 8192^3 384 and 127, 1024 x 16384 x 8192 52
-// and 22.  (The 64 x 64 x 32 configuration, which shares compute units since it has two
-// stages, keeps part of the loss: FP32 3072^3 11.5 ms, 9.7 with three.)  Below
-// HOST_CHECK_FLOPS (130 us in FP32 from device memory, beside which asking for two
-// pointers' memory is nothing) neither is slower by more than 4 %.
+// A large product whose A or B lies in host memory runs on the plan's own configuration,
+// and a direct-load one on the register-staged kernel of its tile (the same bits).  Over
+// the host link the bytes that an L2 loses and asks for again decide, and the direct-load
+// tiles' work-groups, several to a compute unit, drift further apart in k than one large
+// tile per compute unit does.  Direct-load tile, configuration on direct loads, and
+// register-staged (in ms): FP64 8192^3 930, 370-760, 275; FP32 8192^3 384, 130, 129; FP64
+// 6144^3 166-186, 119, 119; FP32 3072^3 11.7, 11.3, 9.4; 1024 x 16384 x 8192 FP64 115, 45.5,
+// 47; FP32 200 x 20000 x 3000 7.5, 7.5, 5.2.  Below HOST_CHECK_FLOPS (130 us in FP32 from
+// device memory, beside which asking for two pointers' memory is nothing) neither is
+// slower by more than 4 %.
 constexpr double HOST_CHECK_FLOPS = 2e10;
 
 static bool large_from_host(const GemmArgs &a) {
@@ -362,11 +363,14 @@ static bool large_from_host(const GemmArgs &a) {
 }
 
 hipError_t launch_whole(const CallPlan &cp, const GemmArgs &a, int32_t dtype, hipStream_t s) {
-    if (!cp.named && !large_from_host(a)) {
+    const bool from_host = large_from_host(a);
+    if (!cp.named && !from_host) {
         bool ran = false;
         const hipError_t he = run_direct(a, dtype, 1, a.k, nullptr, compute_units(), s, &ran);
         if (he != hipSuccess || ran) return he;
     }
+    const LaunchFn host = cp.e->from_host[cp.al ? 0 : 1];
+    if (from_host && host) return host(a, s);
     return (cp.al ? cp.e->launch : cp.e->launch_unaligned)(a, s);
 }
 

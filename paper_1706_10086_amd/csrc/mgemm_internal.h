@@ -64,6 +64,8 @@ struct KernelEntry {
     OccupancyFn batched_occupancy;
     SplitkLaunchFn splitk[2];            // split-k partials, [0] aligned rows, [1] any
                                          // rows; null where the tile has none
+    LaunchFn from_host[2];               // large products whose A or B lies in host
+                                         // memory, likewise; null: as any other
 };
 
 // A part of the tuning-grid registry (grid_*.hip, written by gen_grid.py).
