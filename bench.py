@@ -701,11 +701,12 @@ def main():
         cfg_used, splits, whole_rows = cfg.as_dict(), 1, n
         kernel, tile = kernel_name(cfg_used), (cfg_used["bm"], cfg_used["bn"])
     else:
-        # the default runs its plan on a direct-load tile with the configuration's
-        # bits; large squares take the 128 x 128 one
+        # the default runs its plan on the direct-load tile estimated fastest, with the
+        # configuration's bits: the 128 x 128 one at N = 8192
         c, splits, whole_rows = mg.choice(n, n, n, mg.F64, rows=True)
         cfg_used = c.as_dict()
-        kernel, tile = "gemm_direct_kernel<double,128,128,16,2>", (128, 128)
+        kernel, tile = (("gemm_direct_kernel<double,128,128,16,2>", (128, 128)) if n == 8192
+                        else ("gemm_direct_kernel<double,...>, the tile estimated fastest", None))
     if splits == 1:
         launches = kernel + " (one launch per step)"
     elif whole_rows == 0:
@@ -754,7 +755,7 @@ def main():
                      # Eq. 6 for the kernel's tiles: the bytes with no cache
                      # reuse, against the algorithmic minimum (A, B, C read, C written)
                      "traffic_model": {"tiles_no_reuse": pm.tile_traffic_bytes(
-                                           n, n, n, *tile, 8),
+                                           n, n, n, *tile, 8) if tile else None,
                                        "algorithmic": 4.0 * 8 * n * n}},
         "cpu_baseline": cpu,
     }

@@ -128,8 +128,10 @@ MGEMM_API int32_t gemm(int64_t m, int64_t n, int64_t k, double alpha,
  * of k: the whole products and k ranges of the built-in choice (no cfg, no model)
  * are executed by the direct-load tile estimated fastest for their shape, rows of
  * any alignment, with the bits of the configuration chosen; the chosen one itself
- * runs where the direct loads cannot (see double_buffer), and where A or B of a
- * large product run whole lies in host memory.
+ * runs where the direct loads cannot (see double_buffer).  Large products (2*m*n*k >=
+ * 2e10, run whole) whose A or B lies in host memory run on the chosen configuration,
+ * named or not, and on the register-staged kernel of its tile if that is a
+ * direct-load one, with the same results.
  *
  * Split-k (MGEMM_F64 and MGEMM_F32, cfg == NULL only, k >= 2048 or outside the
  * measured range): when the preferred tile leaves fewer than about four

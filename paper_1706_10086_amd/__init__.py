@@ -195,9 +195,10 @@ class HostBuffer:
 
 def choice(m: int, n: int, k: int, dtype: int = F64, lda: int | None = None,
            ldb: int | None = None, rows: bool = False):
-    """(configuration, k ranges) that gemm with no configuration runs for an
-    m x n x k product with aligned operands (mgemm_choice); with rows, also the
-    rows that run whole (m, 0, or the rows before a split tail)."""
+    """(configuration, k ranges) whose sums gemm with no configuration gives for an
+    m x n x k product with aligned operands (mgemm_choice; a direct-load tile runs
+    them); with rows, also the rows that run whole (m, 0, or the rows before a split
+    tail)."""
     c = Cfg()
     s = ctypes.c_int32()
     r = ctypes.c_int64()
@@ -350,7 +351,8 @@ class _BatchArrays:
 
 
 def gemm_batched(As, Bs, Cs, alphas=1.0, betas=0.0, dtype=None) -> None:
-    """C_i <- alpha_i A_i B_i + beta_i C_i, one library launch per problem."""
+    """C_i <- alpha_i A_i B_i + beta_i C_i as if called in turn; small products that
+    neither read nor rewrite what others of the list write share launches."""
     if not As:
         return
     dtype = dtype_of(As[0]) if dtype is None else dtype

@@ -278,10 +278,12 @@ int32_t gemm_batched_plan_create(int64_t count, const int64_t *m, const int64_t 
                              (long long)i);
         }
         int32_t err = 0;
-        // without caller configurations every problem of a plan uses the 64 x 64 x 16
-        // four-wave tile: in a batch the other problems supply the parallelism, and
-        // one bucket beat mixtures of tile sizes on the uneven batched workload
-        // (28.2 vs 18.8 TFLOP/s with the single-GEMM choice, MI355X)
+        // without caller configurations every problem of a plan uses 64 x 64 tiles
+        // (summed as the 64 x 64 x 16 four-wave configuration): in a batch the other
+        // problems supply the parallelism.  One tile size was set on the persistent
+        // kernels (28.2 TFLOP/s on 2048 uneven problems against 18.8 with the
+        // single-GEMM choice, MI355X; the direct-load tiles run them at 44); by the
+        // direct-load tiles' estimates the best tile per problem would save 6 % there
         const KernelEntry *e =
             choose_entry(dtype, m[i], n[i], cfgs ? &cfgs[i] : &kBatchedDefault, &err);
         if (!e || !e->batched) {

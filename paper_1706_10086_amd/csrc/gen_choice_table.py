@@ -1,7 +1,8 @@
 """Writes choice_table.h: the library's measured configuration choice, distilled
-from the tuner database shipped with the package, in two tables: one for rows the
-three-stage kernels cannot load (FP64: n, lda or ldb odd; FP32: not multiples of 4),
-one for rows they can (consulted by the library only where its preference list
+from the tuner database shipped with the package, in two tables: one for rows that are
+no whole 16-byte loads (FP64: n, lda or ldb odd; FP32: not multiples of 4; the direct-load
+configurations had three stages when the database was measured and took only whole
+ones), one for rows that are (consulted by the library only where its preference list
 names a two-stage configuration).
 
 For each dtype, row class and cell (floor(log2 m), floor(log2 n), floor(log2 k)) with
@@ -48,7 +49,7 @@ NEIGHBOUR_WEIGHT = 0.5
 
 def build_table(records, train_shapes, whole_rows: bool = False, allowed=None):
     """{dtype: {cell: cfg tuple}} from compact-database records, for shapes whose
-    rows the three-stage kernels can (whole_rows) or cannot load; only
+    rows are (whole_rows) or are not whole 16-byte loads; only
     configurations in ``allowed[dtype]`` (default: the registered ones) measured on
     every such training shape compete."""
     import itertools

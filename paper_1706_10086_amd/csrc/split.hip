@@ -1258,7 +1258,9 @@ static int32_t run_split(const GemmArgs &g, hipStream_t s, Workspace &w, int max
 static int32_t run_crt(const GemmArgs &g, hipStream_t s, Workspace &w) {
     const int64_t mp = round_up(g.m, CRT_TILE), np = round_up(g.n, CRT_TILE),
                   kp = round_up(g.k, CRT_KSTEP);
-    // the product kernel addresses a tile's rows of one plane with 32-bit offsets
+    // the bound of the row-major planes of before, whose tiles' rows took 32-bit offsets.
+    // In chunks of 64 k no offset depends on k; the bound stays, since nothing beyond it
+    // has been checked (the least product there has 128 GiB of residues)
     if ((double)CRT_TILE * (double)kp >= 4294967296.0)
         return set_error(MGEMM_ERR_NOCONFIG, "crt int8: k above 2^24 - 64");
     const size_t qa_bytes = (size_t)CRT_MODULI * mp * kp, qb_bytes = (size_t)CRT_MODULI * np * kp;

@@ -8,9 +8,10 @@ configuration; the configuration with the highest prediction is used, and the
 exhaustive sweep remains the fallback and the measure of the prediction's regret.
 
 * features  x = [log2 m, log2 n, log2 k, dtype == F64, dtype == F32, w], w = 1
-            where the rows of A and B are whole 16-byte loads (only then do the
-            three-stage configurations run their own kernels; the tuner's shapes
-            are stored without padding, lda = k, ldb = n), scaled by the training
+            where the rows of A and B are whole 16-byte loads (the direct-load
+            configurations ran only there, with three stages, when the database was
+            measured; the tuner's shapes are stored without padding, lda = k, ldb =
+            n), scaled by the training
             set's mean and standard deviation;
 * targets   r_c^p with r_c = TFLOP/s(c) / max_c' TFLOP/s(c') for every
             configuration c of the shape's dtype (a masked multi-output
